@@ -264,6 +264,9 @@ size_t nexus_suffix_attn_varlen_workspace(int32_t n_seqs, const int32_t *q_start
  *   out         [n_seqs][n_q_heads][head_dim] of the cache dtype.
  *   workspace   at least nexus_decode_attn_workspace() bytes (NULL allowed when that is 0);
  *               contents on entry do not matter.
+ *               Where the bound allows 512 MB of keys and values or more, bf16 launches look for
+ *               physical pages that sequences share (a warm prefix, from page 0 on) and read those
+ *               once for the sequences that map them.
  * bf16 caches: each workgroup reads a KV head's keys and values once for up to 16 query heads
  * (MFMA, fp32 accumulation, probabilities rounded to bf16 as in nexus_suffix_attn).  f32 caches:
  * fp32 VALU kernel.

@@ -15,31 +15,40 @@
 //     of the group are the 16 columns (columns past G are zero).  Lane l then holds the scores
 //     of keys 4 (l / 16) .. +3 for query column l % 16;
 //   * online softmax in log2 units with a lazily moved reference (rescale only when a page's
-//     maximum exceeds the reference by more than 8); P is rounded to bf16 and the row sums add
+//     maximum exceeds the reference by more than kDecSlack); P is rounded to bf16 and the row sums add
 //     the rounded values;
-//   * O^T += V^T.P^T on v_mfma_f32_16x16x16_bf16: the scores are already in the B-operand
-//     layout.  A transposed V cache gives the A operand (4 consecutive keys of one feature)
-//     directly from global memory; a row-major V page is staged in the wave's own LDS slot and
-//     read back with ds_read_b64_tr_b16 (in each 16-lane group, output lane i receives element
-//     i % 4 of the 8 bytes that source lane 4e + i / 4 points at).
-// The 4 waves of a workgroup take the split's pages round-robin, prefetching the next page into
-// registers while computing the current one, and merge their (m, l, O) through LDS at the end.
+//   * O^T += V^T.P^T on v_mfma_f32_16x16x32_bf16, two pages at a time: the scores are already in
+//     the B-operand layout (keys 4 (l / 16) .. +3 of either page).  A transposed V cache gives the
+//     A operand (4 consecutive keys of one feature) directly from global memory; a row-major V page
+//     is staged in the wave's own LDS slot and read back with ds_read_b64_tr_b16 (in each 16-lane
+//     group, output lane i receives element i % 4 of the 8 bytes that source lane 4e + i / 4 points
+//     at).
+// The 4 waves of a workgroup take pairs of the split's pages round-robin, loading the next pair
+// into registers while computing the current one, and merge their (m, l, O) through LDS at the end.
 // Key rows past the sequence end are never used: the last page's loads re-read the last valid
 // row (row-major) or are zeroed (transposed V), and their scores are -inf.
 #include "attn_common.h"
+#include "attn_dma.h"
 #include "launch_decode.h"
+
+#include <algorithm>
 
 namespace nexus {
 
 namespace {
 
-typedef short s16x4 __attribute__((__vector_size__(4 * sizeof(short))));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-
 constexpr int kDecWaves = 4;
-constexpr float kDecSlack = 8.0f;   // log2 units the reference may lag behind the running max
+// log2 units the reference may lag behind the running maximum.  A moved reference gives the key it
+// moves to the probability 1, which bf16 holds exactly, and a few top keys carry much of the
+// rounding error: 32 sequences of 17473 keys, relative error against 64 bits 2.20e-3 at a lag of
+// 8, 2.08e-3 at 6, 2.04e-3 at 4 (2.15e-3 at 8 with pages taken one by one).
+constexpr float kDecSlack = 6.0f;
 constexpr int kMaxDecSplits = 1024; // splits per sequence at most (bounds the merge's loop)
 constexpr int kMaxSplitPages = 2048;  // pages per split at most (page list in LDS)
+constexpr int kMaxSharedPages = 1024; // pages per shared range at most (page list and masks in LDS)
+constexpr int kMaxGroupSeqs = 32;     // sequences whose shared pages one workgroup serves
+constexpr int64_t kSharedMinBytes = (int64_t)512 << 20;   // keys + values of all sequences
+constexpr int kSharedStages = 4;      // ring of page pairs in LDS (shared pages)
 
 struct DecodeArgs {
   const void *q;
@@ -51,7 +60,12 @@ struct DecodeArgs {
   float *part;            // [n_seqs][Hq][max_splits][D] unnormalised split outputs
   float *part_ml;         // [n_seqs][Hq][max_splits][2] (reference m, row sum l)
   int32_t map_stride, max_len, n_q_heads, n_kv_heads, group, n_qgroups;
-  int32_t split_pages, max_splits;
+  int32_t split_pages, max_splits;      // max_splits: partial slots per row
+  int32_t n_seqs;
+  // shared pages (0 groups: none looked for): slots own_splits .. max_splits - 1 of a row belong
+  // to the page ranges of its group
+  int32_t n_groups, group_seqs, shared_splits, shared_split_pages, own_splits;
+  int32_t *flags;         // [n_seqs]: whether a sequence's group shares pages (the merge's use)
   uint32_t n_cols;        // transposed V: NPP * 16
   float scale_log2;       // scale * log2(e)
   float cap_in;           // scale / softcap
@@ -91,34 +105,395 @@ __device__ __forceinline__ int vswz(int r) {
   return D == 64 ? 2 * ((r >> 1) & 3) : 2 * (r & 7);
 }
 
+// Writes the partial (O unnormalised, m, l) of a lane's row; a negative row is skipped.
+template <int D>
+__device__ __forceinline__ void store_part(const DecodeArgs &a, int row, int slot_of_row,
+                                           const f32x4 (&o)[D / 16], float m, float l, int grp) {
+  if (row < 0) return;
+  const size_t slot = (size_t)row * a.max_splits + slot_of_row;
+#pragma unroll
+  for (int t = 0; t < D / 16; ++t)
+    *reinterpret_cast<f32x4 *>(a.part + slot * D + 16 * t + 4 * grp) = o[t];
+  if (grp == 0) {
+    a.part_ml[2 * slot] = m;
+    a.part_ml[2 * slot + 1] = l;
+  }
+}
+// Marks a row's partial slot as empty.
+__device__ __forceinline__ void store_empty(const DecodeArgs &a, int row, int slot_of_row, int grp) {
+  if (row < 0 || grp != 0) return;
+  const size_t slot = (size_t)row * a.max_splits + slot_of_row;
+  a.part_ml[2 * slot] = -INFINITY;
+  a.part_ml[2 * slot + 1] = 0.f;
+}
+
+// ---- pages shared between sequences (a warm prefix).  Consecutive sequences form groups of up to
+// kMaxGroupSeqs; a group's representative is its first sequence with a whole page.  Page p of
+// sequence j counts as shared when it is whole in j and in the representative and both map it to
+// one physical page (the representative's own pages all do); those pages are read once for all
+// the group's queries, every other page by its sequence alone.  A group whose representative's
+// first page is mapped by no other sequence shares nothing: one look at that page settles it.
+struct GroupState {
+  int b0, n;          // first sequence, sequences
+  int rep;            // representative (index in the group)
+  int rep_full;       // its whole pages
+  bool shares;
+};
+// Lane first + j of the wave's 32 lanes from `first` on holds the whole pages and the first page
+// of sequence j of group g.
+__device__ __forceinline__ GroupState group_state(const DecodeArgs &a, int g, int full,
+                                                  int32_t page0, int first) {
+  GroupState s;
+  s.b0 = g * a.group_seqs;
+  s.n = min(a.group_seqs, a.n_seqs - s.b0);
+  const uint64_t in_group = ((1ull << s.n) - 1) << first;      // n <= 32
+  const uint64_t holders = __builtin_amdgcn_ballot_w64(full > 0) & in_group;
+  const int rep_lane = holders ? __builtin_ctzll(holders) : first;
+  s.rep = rep_lane - first;
+  s.rep_full = holders ? __builtin_amdgcn_readlane(full, rep_lane) : 0;
+  const int32_t phys = __builtin_amdgcn_readlane(page0, rep_lane);
+  const uint64_t same = __builtin_amdgcn_ballot_w64(full > 0 && page0 == phys) & in_group;
+  s.shares = __popcll(same) >= 2;
+  return s;
+}
+// Sequence whose length and first page a lane loads for group g (index clamped to the group).
+__device__ __forceinline__ int group_lane_seq(const DecodeArgs &a, int g, int j) {
+  const int b0 = g * a.group_seqs;
+  return b0 + min(j, min(a.group_seqs, a.n_seqs - b0) - 1);
+}
+
+// 16-query column blocks of a wave that serves shared pages.
+__host__ __device__ constexpr int shared_blocks(int head_dim) { return head_dim == 256 ? 2 : 3; }
+
+// Pages of one range of a group's representative, for the query heads hg of all the group's
+// sequences: one 16-query column block holds 16 / G sequences (one when G > 16), the group's column
+// blocks are dealt to the 4 waves and every wave reads every page.  Page pairs travel global -> LDS
+// through a ring of kSharedStages pairs (LDS DMA; wave w fills K (w even) or V (w odd) of page w / 2
+// of the pair), one barrier per pair; per pair a wave forms S^T with 16x16x32 MFMAs, masks the
+// columns whose sequence maps the page elsewhere, and adds V^T.P^T with 16x16x32 MFMAs whose 32
+// keys are the pair's (keys 4 grp .. +3 of either page per lane group, as the scores lie).  Waves
+// keep their own columns, so nothing is merged.  HBM-bound: each page is read once for up to 192
+// (head_dim 256: 128) query columns.  32 sequences of 16385 .. 17473 tokens on one 16384-token
+// prefix, 40 query heads over 8 of head_dim 128: 167 -> 41 us, its merge of 32 ranges 4.8 -> 10.4;
+// 16 sequences of 8000 .. 8192 on one prefix, 16 heads over 8 of head_dim 256, transposed V, capped:
+// 184 -> 58 us a call.
 template <int D, bool VT, bool CAP>
-__global__ __launch_bounds__(256) void decode_bf16_kernel(DecodeArgs a) {
-  constexpr int NB = D == 256 ? 2 : 3;  // pages per wave in registers (1 computed, NB - 1 loading)
+__device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupState &gs, int lane_full,
+                                             int hg, int range, char *smem, int32_t *pgs,
+                                             uint32_t *msk) {
+  constexpr int NCB = shared_blocks(D);
+  constexpr int KS = D / 32, DT = D / 16, KCH = D / 8;
+  constexpr int ROWB = 2 * D;
+  constexpr int PAGEB = 16 * ROWB;              // bytes of a page's K or V of one head
+  constexpr int STAGEB = 4 * PAGEB;             // K, V of page 0, K, V of page 1
+  constexpr int NI = PAGEB / 1024;              // DMA instructions per wave and pair
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qn = lane & 15, grp = lane >> 4;
+  const int h = hg / a.n_qgroups, g_lo = hg % a.n_qgroups * 16;
+  const int g_cnt = min(16, a.group - g_lo);
+  const int per_block = a.group >= 16 ? 1 : 16 / a.group;
+  const int n_blocks = (gs.n + per_block - 1) / per_block;
+  const int p_lo = range * a.shared_split_pages;
+  const int n_pages = min(a.shared_split_pages, gs.rep_full - p_lo);
+  const int slot = a.own_splits + range;
+  // row of query column qn of column block cb: head g_lo + qn % g_cnt of sequence
+  // cb * per_block + qn / g_cnt of the group; -1: none
+  const int in_block = qn / g_cnt;
+  auto seq_of = [&](int cb) {
+    const int j = cb * per_block + in_block;
+    return in_block < per_block && j < gs.n ? j : -1;
+  };
+  auto row_of = [&](int cb) {
+    const int j = seq_of(cb);
+    return j < 0 ? -1 : (gs.b0 + j) * a.n_q_heads + h * a.group + g_lo + qn - in_block * g_cnt;
+  };
+  if (n_pages <= 0) {
+    for (int cb = wave; cb < n_blocks; cb += kDecWaves) store_empty(a, row_of(cb), slot, grp);
+    return;
+  }
+
+  // ---- the range's physical pages and, per page, the sequences that share it: lane = page, wave w
+  // takes sequences 8 w .. 8 w + 7 (byte w of the page's mask)
+  {
+    const int32_t *rep = a.maps + (size_t)(gs.b0 + gs.rep) * a.map_stride + p_lo;
+    for (int i0 = 0; i0 < n_pages; i0 += 64) {
+      const int i = i0 + lane, ic = min(i, n_pages - 1);
+      const int32_t phys = rep[ic];
+      int32_t x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        x[e] = a.maps[(size_t)(gs.b0 + min(8 * wave + e, gs.n - 1)) * a.map_stride + p_lo + ic];
+      uint32_t m = 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int full = __builtin_amdgcn_readlane(lane_full, 8 * wave + e);
+        if (8 * wave + e < gs.n && p_lo + i < full && x[e] == phys) m |= 1u << e;
+      }
+      if (i < n_pages) {
+        if (wave == 0) pgs[i] = phys;
+        reinterpret_cast<uint8_t *>(msk)[4 * i + wave] = (uint8_t)m;
+      }
+    }
+  }
+  // ---- queries of this wave's column blocks wave, wave + 4, ...: B operands
+  u32x4 qreg[NCB][KS];
+  uint32_t bit[NCB];
+#pragma unroll
+  for (int c = 0; c < NCB; ++c) {
+    const int cb = wave + kDecWaves * c;
+    const int row = cb < n_blocks ? row_of(cb) : -1;
+    bit[c] = row >= 0 ? 1u << seq_of(cb) : 0u;
+    const uint16_t *qrow = reinterpret_cast<const uint16_t *>(a.q) + (size_t)max(row, 0) * D;
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      qreg[c][s] = row >= 0 ? *reinterpret_cast<const u32x4 *>(qrow + 32 * s + 8 * grp)
+                            : u32x4{0u, 0u, 0u, 0u};
+  }
+  const int my_blocks = n_blocks > wave ? (n_blocks - wave + kDecWaves - 1) / kDecWaves : 0;
+
+  // ---- DMA: instruction i of a wave covers bytes 1024 i + 16 lane of its K or V page in LDS; the
+  // source chunk is chosen so that K chunk c of row r sits at c ^ (r & 15) (& 7 for head_dim 64),
+  // V chunk c of row r at c ^ vswz(r), transposed V rows (32 bytes a feature) as they are
+  const bool is_v = wave & 1;
+  const char *src = reinterpret_cast<const char *>(is_v ? a.vc : a.kc);
+  uint64_t page_stride = (uint64_t)a.n_kv_heads * PAGEB;
+  src += VT && is_v ? (uint64_t)h * D * a.n_cols * 2 : (uint64_t)h * PAGEB;
+  if (VT && is_v) page_stride = 32;
+  uint32_t voff[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int byte = 1024 * i + 16 * lane;
+    if (VT && is_v) {
+      voff[i] = (uint32_t)(byte >> 5) * a.n_cols * 2u + (byte & 16);
+    } else {
+      const int r = byte / ROWB, c = (byte % ROWB) >> 4;
+      voff[i] = r * ROWB + 16 * (c ^ (is_v ? vswz<D>(r) : (r & (KCH < 16 ? KCH - 1 : 15))));
+    }
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)smem + (wave >> 1) * 2 * PAGEB + (wave & 1) * PAGEB;
+  const int n_pairs = (n_pages + 1) >> 1;
+  wait_vm<0>();      // the DMA loads are counted alone
+  __syncthreads();   // pgs, msk
+  // every step issues one pair (past the end the last page again, unused), so that the counts of
+  // loads in flight are the same throughout
+  auto issue = [&](int i) {
+    const int e = min(2 * i + (wave >> 1), n_pages - 1);
+    const uint64_t phys = (uint32_t)__builtin_amdgcn_readfirstlane(pgs[e]);
+    const char *ps = src + phys * page_stride;
+    const uint32_t dst = lds0 + (i & (kSharedStages - 1)) * STAGEB;
+#pragma unroll
+    for (int n = 0; n < NI; ++n) dma_s<0>(dst + 1024 * n, ps, voff[n]);
+  };
+
+  f32x4 o[NCB][DT];
+  float m_ref[NCB], lsum[NCB];
+#pragma unroll
+  for (int c = 0; c < NCB; ++c) {
+#pragma unroll
+    for (int t = 0; t < DT; ++t) o[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m_ref[c] = -INFINITY;
+    lsum[c] = 0.f;
+  }
+#pragma unroll
+  for (int i = 0; i < kSharedStages - 1; ++i) issue(i);
+  for (int i = 0; i < n_pairs; ++i) {
+    wait_vm<NI *(kSharedStages - 2)>();   // this wave's part of pair i has landed
+    tile_barrier();                       // all parts have, and the slot filled next is read out
+    issue(i + kSharedStages - 1);
+    if (my_blocks == 0) continue;
+    const char *kt = smem + (i & (kSharedStages - 1)) * STAGEB;
+    const char *vt = kt + PAGEB;
+    const uint32_t mask0 = msk[2 * i];
+    const uint32_t mask1 = 2 * i + 1 < n_pages ? msk[2 * i + 1] : 0u;
+    f32x4 s[NCB][2];
+#pragma unroll
+    for (int c = 0; c < NCB; ++c)
+#pragma unroll
+      for (int pp = 0; pp < 2; ++pp) s[c][pp] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int st = 0; st < KS; ++st)
+#pragma unroll
+      for (int pp = 0; pp < 2; ++pp) {
+        const bf16x8 ka = *reinterpret_cast<const bf16x8 *>(
+            kt + 2 * pp * PAGEB + qn * ROWB +
+            16 * ((4 * st + grp) ^ (qn & (KCH < 16 ? KCH - 1 : 15))));
+#pragma unroll
+        for (int c = 0; c < NCB; ++c)
+          s[c][pp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              ka, __builtin_bit_cast(bf16x8, qreg[c][st]), s[c][pp], 0, 0, 0);
+      }
+    bf16x8 pb[NCB];
+#pragma unroll
+    for (int c = 0; c < NCB; ++c) {
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float r = s[c][e >> 2][e & 3];
+        const float v = CAP ? a.cap_out * tanh_fast(r * a.cap_in) : r * a.scale_log2;
+        x[e] = ((e < 4 ? mask0 : mask1) & bit[c]) ? v : -INFINITY;
+      }
+      float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])),
+                       fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
+      mx = max_x32(max_x16(mx));
+      const bool need = mx > m_ref[c] + kDecSlack;
+      if (__builtin_amdgcn_ballot_w64(need)) {
+        const float nm = need ? mx : m_ref[c];
+        // a column that has seen no key yet keeps reference -inf: nothing to rescale
+        const float alpha = nm > -INFINITY ? fast_exp2(m_ref[c] - nm) : 0.f;
+#pragma unroll
+        for (int t = 0; t < DT; ++t) o[c][t] *= alpha;
+        lsum[c] *= alpha;
+        m_ref[c] = nm;
+      }
+      const float nm = m_ref[c] > -INFINITY ? m_ref[c] : 0.f;
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        w[e] = pack_bf16x2(fast_exp2(x[2 * e] - nm), fast_exp2(x[2 * e + 1] - nm));
+        lsum[c] += __uint_as_float(w[e] << 16) + __uint_as_float(w[e] & 0xFFFF0000u);
+      }
+      pb[c] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
+    }
+#pragma unroll
+    for (int t = 0; t < DT; ++t) {
+      bf16x8 va;
+      if constexpr (VT) {
+        const char *p0 = vt + (16 * t + qn) * 32 + 8 * grp;
+        const u32x2 lo = *reinterpret_cast<const u32x2 *>(p0);
+        const u32x2 hi = *reinterpret_cast<const u32x2 *>(p0 + 2 * PAGEB);
+        va = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
+      } else {
+        const int r = 4 * grp + (qn >> 2);
+        const int c = 2 * t + ((qn & 3) >> 1);
+        const char *p0 = vt + r * ROWB + 16 * (c ^ vswz<D>(r)) + 8 * (qn & 1);
+        va = tr_read_pair(p0, p0 + 2 * PAGEB);
+      }
+#pragma unroll
+      for (int c = 0; c < NCB; ++c)
+        o[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb[c], o[c][t], 0, 0, 0);
+    }
+  }
+  wait_vm<0>();      // no DMA may land once the ring is used for something else
+#pragma unroll
+  for (int c = 0; c < NCB; ++c) {
+    const int cb = wave + kDecWaves * c;
+    if (cb < n_blocks)
+      store_part<D>(a, row_of(cb), slot, o[c], m_ref[c], sum_x32(sum_x16(lsum[c])), grp);
+  }
+}
+
+// Appends the pages p_lo + i of [p_lo, p_hi) that `pick` gives a physical page >= 0 for to the lists
+// (physical page, i), in page order; returns the list length.  Called by the whole workgroup.
+template <typename F>
+__device__ __forceinline__ int build_list(int p_lo, int p_hi, int32_t *pgs, uint16_t *lps,
+                                          int32_t *wave_cnt, F pick) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int n = 0;
+  for (int base = p_lo; base < p_hi; base += 256) {
+    const int p = base + threadIdx.x;
+    const int32_t phys = p < p_hi ? pick(p) : -1;
+    const uint64_t m = __builtin_amdgcn_ballot_w64(phys >= 0);
+    if (lane == 0) wave_cnt[wave] = __popcll(m);
+    __syncthreads();
+    int at = n, total = 0;
+#pragma unroll
+    for (int w = 0; w < kDecWaves; ++w) {
+      const int c = wave_cnt[w];
+      if (w < wave) at += c;
+      total += c;
+    }
+    if (phys >= 0) {
+      const int i = at + __popcll(m & ((1ull << lane) - 1));
+      pgs[i] = phys;
+      lps[i] = (uint16_t)(p - p_lo);
+    }
+    n += total;
+    __syncthreads();
+  }
+  return n;
+}
+
+// SH: the launch looks for pages that sequences share (shared_pages); each workgroup first takes
+// a job of the shared pages, if there is one for it, then the rest of its own split's pages.
+template <int D, bool VT, bool CAP, bool SH>
+__device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
+  constexpr int NP = D == 256 ? 1 : 2;   // pages per step of a wave
   constexpr int KS = D / 32;          // S^T MFMA steps
   constexpr int DT = D / 16;          // O^T tiles
   constexpr int ROWB = 2 * D;         // bytes per key row
   constexpr int VL = VT ? 1 : D / 32; // 16-byte V loads per lane per row-major page
   constexpr int MO_LD = D + 4;        // padded row of the merge buffer (floats)
-  constexpr int STAGE_BYTES = kDecWaves * 16 * ROWB;
+  constexpr int STAGE_BYTES = VT ? 0 : kDecWaves * NP * 16 * ROWB;
   constexpr int MERGE_BYTES = 2 * 16 * MO_LD * 4 + 2 * 2 * 16 * 4;
-  constexpr int SMEM = STAGE_BYTES > MERGE_BYTES ? STAGE_BYTES : MERGE_BYTES;
-  __shared__ __align__(16) char smem[SMEM];
+  constexpr int OWN_BYTES = STAGE_BYTES > MERGE_BYTES ? STAGE_BYTES : MERGE_BYTES;
+  constexpr int RING_BYTES = SH ? kSharedStages * 64 * ROWB : 0;
+  constexpr int SMEM = OWN_BYTES > RING_BYTES ? OWN_BYTES : RING_BYTES;
+  __shared__ __align__(1024) char smem[SMEM];
   __shared__ int32_t pgs[kMaxSplitPages];
+  // masks of a shared range's pages, or the logical pages of a split's list
+  __shared__ uint32_t aux[SH ? kMaxSharedPages : 1];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qn = lane & 15, grp = lane >> 4;
-  const int b = blockIdx.z;
-  const int qg = blockIdx.y % a.n_qgroups;
-  const int h = blockIdx.y / a.n_qgroups;
-  const int split = blockIdx.x;
+  int b, hg, split, len;
+  GroupState own{};
+  if constexpr (SH) {
+    // splits vary slowest: the first ids hold the sequences' first pages, which a shared prefix
+    // takes away, and it is they that the jobs go to.  Jobs (group, page range, head) in that
+    // order, job id (and id + grid, ...) to workgroup id; lanes 0 .. 31 look at the job's group,
+    // lanes 32 .. 63 at the own sequence's.
+    const int id = blockIdx.x;
+    const int n_hq = a.n_kv_heads * a.n_qgroups;
+    int rest = id;
+    int kvh = rest % a.n_kv_heads;
+    rest /= a.n_kv_heads;
+    b = rest % a.n_seqs;
+    rest /= a.n_seqs;
+    split = rest % a.own_splits;
+    // Row-major V: odd splits take the heads half a turn on (32 sequences of 17473 tokens, nothing
+    // shared: 386 against 389 us).  Transposed V: an XCD keeps its head, whose 128-byte lines hold
+    // columns of four pages, often other sequences' (391 -> 381 us at 16 x 8192, head_dim 256).
+    if (!VT) kvh = (kvh + (split & 1) * (a.n_kv_heads >> 1)) % a.n_kv_heads;
+    hg = kvh * a.n_qgroups + rest / a.own_splits;
+    const int n_jobs = a.n_groups * a.shared_splits * n_hq;
+    const int own_g = b / a.group_seqs;
+    for (int job = id;; job += gridDim.x) {
+      const int g = job < n_jobs ? job / n_hq / a.shared_splits : own_g;
+      const int lb = group_lane_seq(a, lane & 32 ? own_g : g, lane & 31);
+      const int lane_len = seq_len_of(a, lb);
+      const int32_t page0 = a.maps[(size_t)lb * a.map_stride];
+      if (job == id) {
+        own = group_state(a, own_g, lane_len >> 4, page0, 32);
+        len = __builtin_amdgcn_readlane(lane_len, 32 + b - own.b0);
+        if (split == 0 && hg == 0 && tid == 0) a.flags[b] = own.shares;
+      }
+      if (job >= n_jobs) break;
+      const GroupState gs = group_state(a, g, lane_len >> 4, page0, 0);
+      if (gs.shares) {
+        shared_pages<D, VT, CAP>(a, gs, lane_len >> 4, job % n_hq, job / n_hq % a.shared_splits,
+                                 smem, pgs, aux);
+        __syncthreads();   // the lists and the ring are used again
+      }
+      if (job + (int)gridDim.x >= n_jobs) break;
+    }
+  } else {
+    split = blockIdx.x;
+    hg = blockIdx.y;
+    b = blockIdx.z;
+    len = seq_len_of(a, b);
+  }
+  const int qg = hg % a.n_qgroups;
+  const int h = hg / a.n_qgroups;
   const int g_lo = qg * 16;
   const int g_cnt = min(16, a.group - g_lo);     // query heads of this workgroup
   const int hq0 = h * a.group + g_lo;            // first of them
   uint16_t *out = reinterpret_cast<uint16_t *>(a.out);
 
-  const int len = seq_len_of(a, b);
   if (len == 0) {
     if (split == 0)
       for (int i = tid; i < g_cnt * D; i += 256)
@@ -143,18 +518,35 @@ __global__ __launch_bounds__(256) void decode_bf16_kernel(DecodeArgs a) {
                      : u32x4{0u, 0u, 0u, 0u};
   }
 
-  // the split's physical pages, staged in LDS once
-  const int n_sp = p_end - p_begin;
-  {
-    const int32_t *map = a.maps + (size_t)b * a.map_stride + p_begin;
-    for (int i = tid; i < n_sp; i += 256) pgs[i] = map[i];
+  // the split's physical pages, staged in LDS once (those that its group shares are left out)
+  int n_sp = p_end - p_begin;
+  const int32_t *map = a.maps + (size_t)b * a.map_stride;
+  uint16_t *lps = reinterpret_cast<uint16_t *>(aux);
+  const bool listed = SH && own.shares;
+  if (listed) {
+    const int32_t *rep = a.maps + (size_t)(own.b0 + own.rep) * a.map_stride;
+    const int n_shared = min(len >> 4, own.rep_full);
+    n_sp = build_list(p_begin, p_end, pgs, lps, reinterpret_cast<int32_t *>(smem), [&](int p) {
+      const int32_t mine = map[p];
+      return mine == rep[p] && p < n_shared ? -1 : mine;
+    });
+    if (n_sp == 0) {
+      if (wave == 0 && qn < g_cnt) store_empty(a, b * a.n_q_heads + hq0 + qn, split, grp);
+      return;
+    }
+  } else {
+    for (int i = tid; i < n_sp; i += 256) pgs[i] = map[p_begin + i];
+    __syncthreads();
   }
-  __syncthreads();
+  // logical page of entry i of the list
+  auto logical = [&](int i) {
+    return p_begin + (listed ? __builtin_amdgcn_readfirstlane((int)lps[i]) : i);
+  };
   const uint32_t page_elems = (uint32_t)a.n_kv_heads * 16u * D;
   const char *kbase = reinterpret_cast<const char *>(a.kc) + (size_t)h * 16 * ROWB;
   const char *vbase = VT ? reinterpret_cast<const char *>(a.vc) + (size_t)h * D * a.n_cols * 2
                          : reinterpret_cast<const char *>(a.vc) + (size_t)h * 16 * ROWB;
-  char *vstage = smem + wave * 16 * ROWB;
+  char *vstage = smem + wave * NP * 16 * ROWB;
 
   struct Page {
     u32x4 k[KS];
@@ -193,21 +585,33 @@ __global__ __launch_bounds__(256) void decode_bf16_kernel(DecodeArgs a) {
   float m_ref = -INFINITY;   // reference of query column qn (equal across the 4 lane groups)
   float lsum = 0.f;          // sum of this lane's rounded probabilities
 
-  auto compute_page = [&](int p, const Page &pg) {
-    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+  // Two pages at a time: 32 keys are the k extent of the 16x16x32 MFMA, lane group grp holding keys
+  // 4 grp .. +3 of either page, and one softmax step serves both.  (head_dim 256: one page, whose
+  // two register buffers are as large.)
+  struct Pair {
+    Page pg[NP];
+  };
+  auto compute_pair = [&](const int (&p)[NP], bool two, const Pair &pr) {
+    float x[4 * NP];
+    int key[NP];
 #pragma unroll
-    for (int st = 0; st < KS; ++st)
-      s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pg.k[st]),
-                                                  __builtin_bit_cast(bf16x8, qreg[st]), s, 0, 0,
-                                                  0);
-    const int key0 = 16 * p + 4 * grp;
-    float x[4];
+    for (int pp = 0; pp < NP; ++pp) {
+      key[pp] = 16 * p[pp] + 4 * grp;
+      f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float v = CAP ? a.cap_out * tanh_fast(s[i] * a.cap_in) : s[i] * a.scale_log2;
-      x[i] = key0 + i < len ? v : -INFINITY;
+      for (int st = 0; st < KS; ++st)
+        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pr.pg[pp].k[st]),
+                                                    __builtin_bit_cast(bf16x8, qreg[st]), s, 0, 0,
+                                                    0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float v = CAP ? a.cap_out * tanh_fast(s[i] * a.cap_in) : s[i] * a.scale_log2;
+        x[4 * pp + i] = key[pp] + i < len && (pp == 0 || two) ? v : -INFINITY;
+      }
     }
-    float mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+    float mx = x[0];
+#pragma unroll
+    for (int e = 1; e < 4 * NP; ++e) mx = fmaxf(mx, x[e]);
     mx = max_x32(max_x16(mx));
     const bool need = mx > m_ref + kDecSlack;
     if (__builtin_amdgcn_ballot_w64(need)) {
@@ -218,18 +622,34 @@ __global__ __launch_bounds__(256) void decode_bf16_kernel(DecodeArgs a) {
       lsum *= alpha;
       m_ref = nm;
     }
-    const uint32_t p01 = pack_bf16x2(fast_exp2(x[0] - m_ref), fast_exp2(x[1] - m_ref));
-    const uint32_t p23 = pack_bf16x2(fast_exp2(x[2] - m_ref), fast_exp2(x[3] - m_ref));
-    lsum += (__uint_as_float(p01 << 16) + __uint_as_float(p01 & 0xFFFF0000u)) +
-            (__uint_as_float(p23 << 16) + __uint_as_float(p23 & 0xFFFF0000u));
-    const s16x4 pb = __builtin_bit_cast(s16x4, u32x2{p01, p23});
+    uint32_t w[2 * NP];
+#pragma unroll
+    for (int e = 0; e < 2 * NP; ++e) {
+      w[e] = pack_bf16x2(fast_exp2(x[2 * e] - m_ref), fast_exp2(x[2 * e + 1] - m_ref));
+      lsum += __uint_as_float(w[e] << 16) + __uint_as_float(w[e] & 0xFFFF0000u);
+    }
+    // O^T tile += V^T.P^T with the lane's V of each page, 4 keys of one feature
+    auto pv = [&](f32x4 &acc, const u32x2 (&v)[NP]) {
+      if constexpr (NP == 2)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, u32x4{v[0][0], v[0][1], v[NP - 1][0], v[NP - 1][1]}),
+            __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2 * NP - 2], w[2 * NP - 1]}), acc, 0, 0,
+            0);
+      else
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, v[0]),
+                                                        __builtin_bit_cast(s16x4, u32x2{w[0], w[1]}),
+                                                        acc, 0, 0, 0);
+    };
     if constexpr (!VT) {
 #pragma unroll
-      for (int j = 0; j < VL; ++j) {
-        const int byte = 16 * lane + 1024 * j;
-        const int row = byte / ROWB, c = (byte % ROWB) >> 4;
-        *reinterpret_cast<u32x4 *>(vstage + row * ROWB + 16 * (c ^ vswz<D>(row))) = pg.v[j];
-      }
+      for (int pp = 0; pp < NP; ++pp)
+#pragma unroll
+        for (int j = 0; j < VL; ++j) {
+          const int byte = 16 * lane + 1024 * j;
+          const int row = byte / ROWB, c = (byte % ROWB) >> 4;
+          *reinterpret_cast<u32x4 *>(vstage + pp * 16 * ROWB + row * ROWB +
+                                     16 * (c ^ vswz<D>(row))) = pr.pg[pp].v[j];
+        }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       const int r = 4 * grp + (qn >> 2);
@@ -237,54 +657,76 @@ __global__ __launch_bounds__(256) void decode_bf16_kernel(DecodeArgs a) {
       for (int t = 0; t < DT; ++t) {
         const int c = 2 * t + ((qn & 3) >> 1);
         const char *src = vstage + r * ROWB + 16 * (c ^ vswz<D>(r)) + 8 * (qn & 1);
-        const s16x4 va = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)src);
-        o[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(va, pb, o[t], 0, 0, 0);
+        u32x2 v[NP];
+#pragma unroll
+        for (int pp = 0; pp < NP; ++pp)
+          v[pp] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                                (lds_s16x4 *)(src + pp * 16 * ROWB)));
+        pv(o[t], v);
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     } else {
       // slots past the sequence end may hold anything: zero this lane's keys beyond it
-      const int keep = len - key0;
-      const uint32_t m0 = keep >= 2 ? 0xFFFFFFFFu : keep == 1 ? 0x0000FFFFu : 0u;
-      const uint32_t m1 = keep >= 4 ? 0xFFFFFFFFu : keep == 3 ? 0x0000FFFFu : 0u;
+      u32x2 m[NP];
+#pragma unroll
+      for (int pp = 0; pp < NP; ++pp) {
+        const int keep = len - key[pp];
+        m[pp][0] = keep >= 2 ? 0xFFFFFFFFu : keep == 1 ? 0x0000FFFFu : 0u;
+        m[pp][1] = keep >= 4 ? 0xFFFFFFFFu : keep == 3 ? 0x0000FFFFu : 0u;
+      }
 #pragma unroll
       for (int t = 0; t < DT; ++t) {
-        const u32x2 w = u32x2{pg.vt[t][0] & m0, pg.vt[t][1] & m1};
-        o[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, w), pb, o[t],
-                                                         0, 0, 0);
+        u32x2 v[NP];
+#pragma unroll
+        for (int pp = 0; pp < NP; ++pp)
+          v[pp] = u32x2{pr.pg[pp].vt[t][0] & m[pp][0], pr.pg[pp].vt[t][1] & m[pp][1]};
+        pv(o[t], v);
       }
     }
   };
 
-  // ---- this wave's pages p_begin + wave + 4 k, k = 0 .. n_mine - 1: a ring of NB register
-  // buffers keeps NB - 1 pages in flight while one is computed.  Every step issues exactly one
-  // page of loads (past the end it re-reads the wave's last page, unused), so the wait before
-  // each computation leaves the younger pages in flight.
+  // ---- this wave's pairs of list entries wave + 4 k, k = 0 .. n_mine - 1, through two register
+  // buffers: a pair is loading while the other is computed.  Every step issues one pair of loads
+  // (entries past the list's end re-read its last page, masked or unused), so the wait before each
+  // computation leaves the younger pair in flight.
   {
-    const int first = wave;
-    const int n_mine = first < n_sp ? (n_sp - first + kDecWaves - 1) / kDecWaves : 0;
+    const int n_pairs = (n_sp + NP - 1) / NP;
+    const int n_mine = wave < n_pairs ? (n_pairs - wave + kDecWaves - 1) / kDecWaves : 0;
     if (n_mine > 0) {
-      Page buf[NB];
-      auto issue = [&](int k, Page &pg) {
-        const int lp = first + kDecWaves * min(k, n_mine - 1);   // page within the split
-        const uint32_t phys = (uint32_t)__builtin_amdgcn_readfirstlane(pgs[lp]);
-        load_page(p_begin + lp, phys, pg);
-      };
+      auto entry = [&](int k) { return NP * (wave + kDecWaves * k); };
+      auto issue = [&](int k, Pair &pr) {
 #pragma unroll
-      for (int i = 0; i < NB - 1; ++i) issue(i, buf[i]);
-      bool more = true;
-      for (int k0 = 0; more; k0 += NB) {
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-          const int k = k0 + j;
-          if (k >= n_mine) {
-            more = false;
-            break;
-          }
-          issue(k + NB - 1, buf[(j + NB - 1) % NB]);
-          compute_page(p_begin + first + kDecWaves * k, buf[j]);
+        for (int pp = 0; pp < NP; ++pp) {
+          const int e = min(entry(min(k, n_mine - 1)) + pp, n_sp - 1);
+          load_page(logical(e), (uint32_t)__builtin_amdgcn_readfirstlane(pgs[e]), pr.pg[pp]);
         }
+      };
+      auto compute = [&](int k, const Pair &pr) {
+        const int e = entry(k);
+        int p[NP];
+#pragma unroll
+        for (int pp = 0; pp < NP; ++pp) p[pp] = logical(min(e + pp, n_sp - 1));
+        compute_pair(p, e + 1 < n_sp, pr);
+      };
+      Pair b0, b1;
+      issue(0, b0);
+      // The scheduling barriers keep a pair's loads ahead of the other pair's computation, which the
+      // scheduler would otherwise start first, to reuse its registers as they are read; one loop
+      // exit, because a second one is routed through a block that also leads back into the loop,
+      // and the waits for loads then count that path too.
+      int k = 0;
+      for (; k + 1 < n_mine; k += 2) {
+        issue(k + 1, b1);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(k, b0);
+        __builtin_amdgcn_sched_barrier(0);
+        issue(k + 2, b0);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(k + 1, b1);
+        __builtin_amdgcn_sched_barrier(0);
       }
+      if (k < n_mine) compute(k, b0);
     }
   }
 
@@ -328,24 +770,26 @@ __global__ __launch_bounds__(256) void decode_bf16_kernel(DecodeArgs a) {
   if (wave != 0) return;
   merge_state(0);
   if (!q_ok) return;
-  const size_t row = (size_t)b * a.n_q_heads + hq0 + qn;
-  if (n_splits == 1) {
+  const int row = b * a.n_q_heads + hq0 + qn;
+  if (n_splits == 1 && !listed) {
     const float inv = 1.0f / lsum;
 #pragma unroll
     for (int t = 0; t < DT; ++t)
-      *reinterpret_cast<u32x2 *>(out + row * D + 16 * t + 4 * grp) =
+      *reinterpret_cast<u32x2 *>(out + (size_t)row * D + 16 * t + 4 * grp) =
           u32x2{pack_bf16x2(o[t][0] * inv, o[t][1] * inv),
                 pack_bf16x2(o[t][2] * inv, o[t][3] * inv)};
   } else {
-    const size_t slot = row * a.max_splits + split;
-#pragma unroll
-    for (int t = 0; t < DT; ++t)
-      *reinterpret_cast<f32x4 *>(a.part + slot * D + 16 * t + 4 * grp) = o[t];
-    if (grp == 0) {
-      a.part_ml[2 * slot] = m_ref;
-      a.part_ml[2 * slot + 1] = lsum;
-    }
+    store_part<D>(a, row, split, o, m_ref, lsum, grp);
   }
+}
+
+template <int D, bool VT, bool CAP>
+__global__ __launch_bounds__(256, D == 64 ? 3 : D == 128 ? 2 : 1) void decode_bf16_kernel(DecodeArgs a) {
+  decode_bf16<D, VT, CAP, false>(a);
+}
+template <int D, bool VT, bool CAP>
+__global__ __launch_bounds__(256, D < 256 ? 2 : 1) void decode_bf16_shared_kernel(DecodeArgs a) {
+  decode_bf16<D, VT, CAP, true>(a);
 }
 
 // fp32 caches: one wave per (sequence, query head, split), VALU dot products.  Lane l holds key
@@ -420,72 +864,98 @@ __global__ __launch_bounds__(64) void decode_f32_kernel(DecodeArgs a, int D) {
   }
 }
 
-// Merge of the splits of every (sequence, query head) that has more than one: one wave per
-// (sequence, query head), lane l owning features l, l + 64, ...  The first kPre splits' outputs
-// are loaded together with the (m, l) pairs, so that the round trips to memory overlap; the
-// maximum and the weighted row sum are wave reductions and split s's weight is read from the
-// lane that formed it.
+// Merge of the partials of every (sequence, query head) that has more than one split, or any under
+// shared pages: one wave per (sequence, query head).  D / 4 lanes cover a partial row in 16-byte
+// loads, so a wave reads 64 / (D / 4) partials per instruction; the first kPre instructions are
+// issued with the (m, l) pairs, so that the round trips to memory overlap.  Lane k holds the
+// weight of slot 64 c + k; partials are added in order within each of the wave's shares, the
+// shares at the end.  A partial with m = -inf holds nothing (no page was left to it) and its
+// output is never used.
 template <bool BF16>
-__global__ __launch_bounds__(64) void decode_combine_kernel(DecodeArgs a, int D) {
-  constexpr int kPre = 16;          // splits whose outputs are loaded up front
+__global__ __launch_bounds__(64) void decode_combine_kernel(DecodeArgs a, int D, int lpr_shift) {
+  constexpr int kPre = 20, kQuad = 4;   // load instructions in flight together; skipped by fours
   const int lane = threadIdx.x;
   const int hq = blockIdx.x, b = blockIdx.y;
+  const size_t row = (size_t)b * a.n_q_heads + hq;
+  const float2 *ml = reinterpret_cast<const float2 *>(a.part_ml) + row * a.max_splits;
+  const float *po = a.part + row * a.max_splits * D;
+  const int share = lane >> lpr_shift, n_shares = 64 >> lpr_shift;
+  const int d = 4 * (lane & ((1 << lpr_shift) - 1));
+  f32x4 pre[kPre];
+  auto load = [&](int s0, int end) {
+#pragma unroll
+    for (int i0 = 0; i0 < kPre; i0 += kQuad) {
+      if (s0 + i0 * n_shares >= end) continue;
+#pragma unroll
+      for (int i = i0; i < i0 + kQuad; ++i) {
+        const int s = s0 + i * n_shares + share;
+        if (s < end) pre[i] = *reinterpret_cast<const f32x4 *>(po + (size_t)s * D + d);
+      }
+    }
+  };
+  // The first loads do not wait for the sequence's length (a slot that turns out to hold nothing
+  // is not used), so the launch is one round trip for all but the longest rows.
+  load(0, a.own_splits);
+  float2 ml0 = lane < a.max_splits ? ml[lane] : float2{-INFINITY, 0.f};
+  bool shares = false;              // whether the row's group has partials of shared pages
+  if (a.n_groups > 0) shares = a.flags[b] != 0;
   const int len = seq_len_of(a, b);
   const int n_pages = (len + 15) >> 4;
-  const int ns = (n_pages + a.split_pages - 1) / a.split_pages;
-  if (ns <= 1) return;
-  const size_t row = (size_t)b * a.n_q_heads + hq;
-  const float *ml = a.part_ml + 2 * row * a.max_splits;
-  const float *po = a.part + row * a.max_splits * D;
-  const int dpl = D > 64 ? D / 64 : 1;          // features per lane: 1, 2 or 4
-  const bool dok = lane < D;
-  float pre[kPre][4];
-#pragma unroll
-  for (int i = 0; i < kPre; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      pre[i][j] = (i < ns && j < dpl && dok) ? po[(size_t)i * D + lane + 64 * j] : 0.f;
-  float m = -INFINITY;
-  for (int s = lane; s < ns; s += 64) m = fmaxf(m, ml[2 * s]);
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  const float M = m;
-  float lsum = 0.f;
-  for (int s = lane; s < ns; s += 64) lsum += ml[2 * s + 1] * fast_exp2(ml[2 * s] - M);
-  for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
-  float o[4] = {0.f, 0.f, 0.f, 0.f};
-  // lane k holds the weight of split 64 c + k of the current chunk c of 64 splits
-  float wl = lane < ns ? fast_exp2(ml[2 * lane] - M) : 0.f;
-  for (int s0 = 0; s0 < ns; s0 += kPre) {
-    if (s0 > 0) {
-      // the next kPre splits' outputs, all loads in flight together
-#pragma unroll
-      for (int i = 0; i < kPre; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          pre[i][j] = (s0 + i < ns && j < dpl && dok)
-                          ? po[(size_t)(s0 + i) * D + lane + 64 * j] : 0.f;
-      if ((s0 & 63) == 0) wl = s0 + lane < ns ? fast_exp2(ml[2 * (s0 + lane)] - M) : 0.f;
-    }
+  const int n_own = (n_pages + a.split_pages - 1) / a.split_pages;
+  if (n_own == 0 || (n_own == 1 && !shares)) return;
+  // the row's partials: slots below n_own and, with shared pages, those from own_splits on
+  const int ns = shares ? a.max_splits : n_own;
+  auto used = [&](int s) { return s < n_own || (s >= a.own_splits && s < ns); };
+  if (shares && kPre * n_shares > a.own_splits) {
 #pragma unroll
     for (int i = 0; i < kPre; ++i) {
-      // splits past ns hold zeros
-      const float w =
-          __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wl), (s0 + i) & 63));
-#pragma unroll
-      for (int j = 0; j < 4; ++j) o[j] += pre[i][j] * w;
+      const int s = i * n_shares + share;
+      if (s >= a.own_splits && s < ns)
+        pre[i] = *reinterpret_cast<const f32x4 *>(po + (size_t)s * D + d);
     }
   }
-  if (!dok) return;
+  // the first 64 pairs stay in registers, the others (very long sequences) are read again
+  if (!used(lane)) ml0 = float2{-INFINITY, 0.f};
+  float M = ml0.x;
+  for (int s = lane + 64; s < ns; s += 64)
+    if (used(s)) M = fmaxf(M, ml[s].x);
+  for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
+  float lsum = used(lane) ? ml0.y * fast_exp2(ml0.x - M) : 0.f;
+  for (int s = lane + 64; s < ns; s += 64)
+    if (used(s)) lsum += ml[s].y * fast_exp2(ml[s].x - M);
+  for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  // -1: an empty partial
+  auto weight = [&](float m) { return m == -INFINITY ? -1.f : fast_exp2(m - M); };
+  float wl = weight(ml0.x);
+  int w0 = 0;                       // partial whose weight lane 0 holds
+  for (int s0 = 0; s0 < ns; s0 += kPre * n_shares) {
+    if (s0 > 0) load(s0, ns);
+#pragma unroll
+    for (int i0 = 0; i0 < kPre; i0 += kQuad) {
+      if (s0 + i0 * n_shares >= ns) continue;
+#pragma unroll
+      for (int i = i0; i < i0 + kQuad; ++i) {
+        const int s1 = s0 + i * n_shares;
+        if (s1 < ns && s1 - w0 >= 64) {   // (n_shares divides 64)
+          w0 += 64;
+          wl = weight(used(w0 + lane) ? ml[w0 + lane].x : -INFINITY);
+        }
+        const float w = __shfl(wl, (s1 - w0 + share) & 63);
+        if (used(s1 + share) && w != -1.f) o += pre[i] * w;
+      }
+    }
+  }
+  for (int off = 32; off >= 1 << lpr_shift; off >>= 1)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] += __shfl_xor(o[e], off);
+  if (share != 0) return;
   const float inv = 1.0f / lsum;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if (j < dpl) {
-      const float r = o[j] * inv;
-      if (BF16) reinterpret_cast<uint16_t *>(a.out)[row * D + lane + 64 * j] =
-          (uint16_t)(pack_bf16x2(r, 0.f) & 0xFFFFu);
-      else reinterpret_cast<float *>(a.out)[row * D + lane + 64 * j] = r;
-    }
-  }
+  if (BF16)
+    *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(a.out) + row * D + d) =
+        u32x2{pack_bf16x2(o[0] * inv, o[1] * inv), pack_bf16x2(o[2] * inv, o[3] * inv)};
+  else
+    *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.out) + row * D + d) = o * inv;
 }
 
 }  // namespace
@@ -519,31 +989,60 @@ int decode_split_pages(int32_t n_seqs, int32_t n_kv_heads, int32_t wgs_per_kv_he
 
 namespace {
 
-// Splits of the launch: `sp` pages per split, `max_splits` over the longest sequence.
-void decode_geometry(const DecodeLaunch &p, int &sp, int &max_splits) {
+// Shape of a launch: splits of each sequence's own pages, and the groups and page ranges of the
+// pages that sequences share.
+struct DecodeShape {
+  int split_pages, own_splits;         // pages per split, splits of the longest sequence
+  int n_groups, group_seqs;            // 0 groups: shared pages are not looked for
+  int shared_split_pages, shared_splits;
+  int slots() const { return own_splits + (n_groups ? shared_splits : 0); }
+};
+
+DecodeShape decode_shape(const DecodeLaunch &p) {
+  DecodeShape s{};
   const int group = p.n_q_heads / p.n_kv_heads;
   // bf16: one workgroup per 16 query heads of a group; f32: one wave per query head
   const int per_kv = p.is_bf16 ? (group + 15) / 16 : group;
-  sp = decode_split_pages(p.n_seqs, p.n_kv_heads, per_kv, p.max_len);
+  s.split_pages = decode_split_pages(p.n_seqs, p.n_kv_heads, per_kv, p.max_len);
   const int64_t max_pages = ((int64_t)p.max_len + 15) / 16;
-  max_splits = (int)((max_pages + sp - 1) / sp);
-  if (max_splits < 1) max_splits = 1;
+  s.own_splits = (int)((max_pages + s.split_pages - 1) / s.split_pages);
+  if (s.own_splits < 1) s.own_splits = 1;
+  // Looking for shared pages costs 2 to 3 us a launch where nothing is shared, and below some
+  // 100 us the caches serve the repeated reads anyway: only where the sequences' keys and values
+  // together pass twice the 256 MB last-level cache
+  const int64_t kv_bytes = (int64_t)p.n_seqs * p.max_len * p.n_kv_heads * p.head_dim * 4;
+  if (!p.is_bf16 || p.n_seqs < 2 || kv_bytes < kSharedMinBytes) return s;
+  // sequences per group: what the column blocks of a workgroup hold
+  const int per_block = group >= 16 ? 1 : 16 / group;
+  const int cap = std::min(kMaxGroupSeqs, kDecWaves * shared_blocks(p.head_dim) * per_block);
+  s.n_groups = (p.n_seqs + cap - 1) / cap;
+  s.group_seqs = (p.n_seqs + s.n_groups - 1) / s.n_groups;
+  s.n_groups = (p.n_seqs + s.group_seqs - 1) / s.group_seqs;
+  // about one job of shared pages per CU
+  const int64_t heads = (int64_t)s.n_groups * p.n_kv_heads * per_kv;
+  const int64_t ns = heads < 256 ? 256 / heads : 1;
+  int64_t sp = (max_pages + ns - 1) / ns;
+  if (sp < 16) sp = 16;
+  if (sp > kMaxSharedPages) sp = kMaxSharedPages;
+  s.shared_split_pages = (int)sp;
+  s.shared_splits = (int)((max_pages + s.shared_split_pages - 1) / s.shared_split_pages);
+  return s;
 }
 
 }  // namespace
 
 size_t decode_workspace_bytes(const DecodeLaunch &p) {
-  int sp, max_splits;
-  decode_geometry(p, sp, max_splits);
-  if (max_splits <= 1) return 0;
-  return (size_t)p.n_seqs * p.n_q_heads * max_splits * (p.head_dim + 2) * sizeof(float);
+  const DecodeShape s = decode_shape(p);
+  if (s.slots() <= 1) return 0;
+  return (size_t)p.n_seqs * p.n_q_heads * s.slots() * (p.head_dim + 2) * sizeof(float) +
+         (s.n_groups ? (size_t)p.n_seqs * sizeof(int32_t) : 0);
 }
 
 hipError_t launch_decode(const DecodeLaunch &p, hipStream_t stream) {
   const int group = p.n_q_heads / p.n_kv_heads;
   const int n_qgroups = (group + 15) / 16;
-  int sp, max_splits;
-  decode_geometry(p, sp, max_splits);
+  const DecodeShape sh = decode_shape(p);
+  const int slots = sh.slots();
   DecodeArgs a{};
   const size_t esize = p.is_bf16 ? 2 : 4;
   const size_t layer_elems = (size_t)p.n_phys_pages * p.n_kv_heads * 16 * p.head_dim;
@@ -554,17 +1053,25 @@ hipError_t launch_decode(const DecodeLaunch &p, hipStream_t stream) {
   a.maps = p.maps;
   a.lens = p.lens;
   float *ws = reinterpret_cast<float *>(p.workspace);
-  const size_t part_elems = (size_t)p.n_seqs * p.n_q_heads * max_splits * p.head_dim;
-  a.part = max_splits > 1 ? ws : nullptr;
-  a.part_ml = max_splits > 1 ? ws + part_elems : nullptr;
+  const size_t part_elems = (size_t)p.n_seqs * p.n_q_heads * slots * p.head_dim;
+  a.part = slots > 1 ? ws : nullptr;
+  a.part_ml = slots > 1 ? ws + part_elems : nullptr;
+  a.flags = reinterpret_cast<int32_t *>(
+      ws + part_elems + (size_t)2 * p.n_seqs * p.n_q_heads * slots);
   a.map_stride = p.map_stride;
   a.max_len = p.max_len;
   a.n_q_heads = p.n_q_heads;
   a.n_kv_heads = p.n_kv_heads;
   a.group = group;
   a.n_qgroups = n_qgroups;
-  a.split_pages = sp;
-  a.max_splits = max_splits;
+  a.split_pages = sh.split_pages;
+  a.max_splits = slots;
+  a.n_seqs = p.n_seqs;
+  a.n_groups = sh.n_groups;
+  a.group_seqs = sh.group_seqs;
+  a.shared_splits = sh.shared_splits;
+  a.shared_split_pages = sh.shared_split_pages;
+  a.own_splits = sh.own_splits;
   a.n_cols = (uint32_t)p.n_phys_pages * 16u;
   const float log2e = 1.4426950408889634f;
   a.scale_log2 = p.scale * log2e;
@@ -572,9 +1079,18 @@ hipError_t launch_decode(const DecodeLaunch &p, hipStream_t stream) {
   a.cap_out = p.softcap * log2e;
   const bool cap = p.softcap > 0.f;
   if (p.is_bf16) {
-    const dim3 grid(max_splits, p.n_kv_heads * n_qgroups, p.n_seqs);
-#define NEXUS_DEC(D_, VT_, CAP_) \
-  hipLaunchKernelGGL((decode_bf16_kernel<D_, VT_, CAP_>), grid, dim3(256), 0, stream, a)
+    const int n_hq = p.n_kv_heads * n_qgroups;
+    const bool shared = sh.n_groups > 0;
+    const dim3 grid =
+        shared ? dim3((uint32_t)n_hq * p.n_seqs * sh.own_splits)
+               : dim3(sh.own_splits, n_hq, p.n_seqs);
+#define NEXUS_DEC(D_, VT_, CAP_)                                                                   \
+  do {                                                                                             \
+    if (shared)                                                                                    \
+      hipLaunchKernelGGL((decode_bf16_shared_kernel<D_, VT_, CAP_>), grid, dim3(256), 0, stream, a); \
+    else                                                                                           \
+      hipLaunchKernelGGL((decode_bf16_kernel<D_, VT_, CAP_>), grid, dim3(256), 0, stream, a); \
+  } while (0)
 #define NEXUS_DEC_D(D_)                                             \
   do {                                                              \
     if (p.v_transposed) {                                           \
@@ -589,7 +1105,7 @@ hipError_t launch_decode(const DecodeLaunch &p, hipStream_t stream) {
 #undef NEXUS_DEC_D
 #undef NEXUS_DEC
   } else {
-    const dim3 grid(max_splits, p.n_q_heads, p.n_seqs);
+    const dim3 grid(sh.own_splits, p.n_q_heads, p.n_seqs);
     if (p.v_transposed) {
       if (cap) hipLaunchKernelGGL((decode_f32_kernel<true, true>), grid, dim3(64), 0, stream, a, p.head_dim);
       else hipLaunchKernelGGL((decode_f32_kernel<true, false>), grid, dim3(64), 0, stream, a, p.head_dim);
@@ -599,12 +1115,16 @@ hipError_t launch_decode(const DecodeLaunch &p, hipStream_t stream) {
     }
   }
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || max_splits <= 1) return e;
+  if (e != hipSuccess || slots <= 1) return e;
   const dim3 cgrid(p.n_q_heads, p.n_seqs);
+  int lpr_shift = 0;                  // log2 of the lanes that cover a partial row
+  while ((4 << lpr_shift) < p.head_dim) ++lpr_shift;
   if (p.is_bf16)
-    hipLaunchKernelGGL((decode_combine_kernel<true>), cgrid, dim3(64), 0, stream, a, p.head_dim);
+    hipLaunchKernelGGL((decode_combine_kernel<true>), cgrid, dim3(64), 0, stream, a, p.head_dim,
+                       lpr_shift);
   else
-    hipLaunchKernelGGL((decode_combine_kernel<false>), cgrid, dim3(64), 0, stream, a, p.head_dim);
+    hipLaunchKernelGGL((decode_combine_kernel<false>), cgrid, dim3(64), 0, stream, a, p.head_dim,
+                       lpr_shift);
   return hipGetLastError();
 }
 

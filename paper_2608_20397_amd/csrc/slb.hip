@@ -6,23 +6,23 @@
 // rounded to nearest-even; the integer dot is exact and, with |dot| <= 127^2 * 1024 < 2^24,
 // exactly representable in fp32.
 //
-// Both scan kernels compute S^T = T.Q^T on v_mfma_i32_16x16x64_i8 (tool rows straight from
+// The scan kernels compute S^T = T.Q^T on v_mfma_i32_16x16x64_i8 (tool rows straight from
 // global memory into the A-operand registers, the query block staged in LDS as the B operands),
 // loading ahead while they compute.  Lane l then holds tools 4 (l / 16) .. +3 of a 16-tool tile
-// for query column l % 16 and folds them into its own sorted list of the best KT (higher score
-// first, lower index first among equal scores: both orders are carried by one 64-bit key, so
-// the list update is a branch-free max/min pass).  A column's 4 lane lists are merged by lane
-// exchanges and the 4 waves' lists through LDS.  With one tool range the result is final
-// (top-k, margin, gate); otherwise each range's best 8 go to the workspace and a second kernel
-// merges them the same way.
+// for query column l % 16.  A candidate is one 64-bit key that carries both orders (higher score
+// first, lower index first among equal scores), so the best are found by comparing keys alone.
 //
-// * Up to 16 queries (the single-query lookup of a user turn): one 16-query block; the waves
-//   take the range's 16-tool tiles in turn, each tile one MFMA chain.  HBM-bound for one query.
-// * More queries: a workgroup holds 64 queries and its 4 waves take 64-tool blocks of the range
-//   in turn; for one block a wave keeps 16 MFMA chains (4 tool tiles x 4 query sub-blocks) and
-//   walks the dimension two 64-byte steps at a time, holding those steps of its 64 tool rows in
-//   registers (the next two in flight), so every B operand read from LDS feeds four MFMAs and
-//   every tool row is read once per workgroup.
+// * Up to 16 queries (the single-query lookup of a user turn), and any number over a registry of
+//   one range: one 16-query block per workgroup column; the waves take the range's 16-tool tiles
+//   in turn, each tile one MFMA chain, and fold the scores into each lane's own sorted list of the
+//   best KT.  A column's 4 lane lists are merged by lane exchanges and the 4 waves' lists through
+//   LDS.  With one range the result is final (top-k, margin, gate); otherwise each range's best
+//   go to the workspace and a second kernel merges them.  HBM-bound for one query.
+// * More queries: two passes without any list in the first (slb_max_kernel, slb_select_kernel).
+//   The first writes the best score of every 16-tool tile for every query; the second takes the
+//   KT best tiles of a query, which hold its KT best tools (a tool of any other tile has KT tools
+//   ranking above it, one in each of those tiles: equal scores go to the lower tile as to the lower
+//   index), scores their KT x 16 tools again and ranks them.
 #include "device_common.h"
 #include "launch_slb.h"
 
@@ -116,6 +116,8 @@ struct SlbArgs {
   float *margin;
   int32_t *route;
   uint64_t *part;                     // [n_queries][n_ranges][KT] candidate keys
+  uint32_t *tile_max;                 // batches: [n_queries][tile_ld] best score of each tile
+  int32_t tile_ld, n_qblocks;         // 16-tool tiles of whole 64-tool blocks; 64-query blocks
 };
 
 // Final outputs of one query from its sorted best keys (lane 0 writes).
@@ -175,7 +177,8 @@ __device__ __forceinline__ void merge_lanes(uint64_t (&b)[KT], int off) {
   }
 }
 
-// Small batches (at most 16 queries: one 16-query block, the single-query lookup of a user turn).
+// Small batches (the single-query lookup of a user turn): workgroup = range; registries of one range:
+// workgroup = 16-query block.
 // MAXS: 64-byte steps of dim at most (dim <= 64 MAXS); KT: candidates kept, >= max(k, 2).  The
 // query block sits in LDS; wave w takes the range's 16-tool tiles w, w + 4, ..., loading each
 // tile's rows straight into the A-operand registers (the next tile in flight) and running one
@@ -187,7 +190,8 @@ __global__ __launch_bounds__(256) void slb_scan_kernel(SlbArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qn = lane & 15, grp = lane >> 4;
-  const int range = blockIdx.x;
+  const int range = a.n_ranges > 1 ? blockIdx.x : 0;
+  const int q0 = a.n_ranges > 1 ? 0 : 16 * blockIdx.x, n_q = min(16, a.n_queries - q0);
   const int t_begin = range * a.range_tools;
   const int t_end = min(t_begin + a.range_tools, a.n_tools);
   const int dim = a.dim, steps = dim / 64, ld = dim + kQPad;
@@ -196,10 +200,10 @@ __global__ __launch_bounds__(256) void slb_scan_kernel(SlbArgs a) {
   for (int c = tid; c < 16 * (dim / 16); c += 256) {
     const int r = c / (dim / 16), off = (c - r * (dim / 16)) * 16;
     u32x4 v = u32x4{0u, 0u, 0u, 0u};
-    if (r < a.n_queries) v = *reinterpret_cast<const u32x4 *>(a.queries + (size_t)r * dim + off);
+    if (r < n_q) v = *reinterpret_cast<const u32x4 *>(a.queries + (size_t)(q0 + r) * dim + off);
     *reinterpret_cast<u32x4 *>(qs + r * ld + off) = v;
   }
-  const float sq = qn < a.n_queries ? a.query_scale[qn] : 0.f;
+  const float sq = qn < n_q ? a.query_scale[q0 + qn] : 0.f;
   __syncthreads();
 
   uint64_t best[KT];
@@ -272,8 +276,8 @@ __global__ __launch_bounds__(256) void slb_scan_kernel(SlbArgs a) {
 #pragma unroll
     for (int j = 0; j < KT; ++j) cl[(wave * 16 + qn) * KT + j] = best[j];
   __syncthreads();
-  if (wave > 0 || grp != 0 || qn >= a.n_queries) return;
-  const int q = qn;
+  if (wave > 0 || grp != 0 || qn >= n_q) return;
+  const int q = q0 + qn;
   for (int w = 1; w < kWaves; ++w)
 #pragma unroll
     for (int j = 0; j < KT; ++j) {
@@ -303,13 +307,24 @@ __global__ __launch_bounds__(256) void slb_scan_kernel(SlbArgs a) {
   }
 }
 
-// Batched scan.  Range tool scales are staged in LDS next to the query block, so the candidate
-// pass reads them without a global load.  Lane (qn, grp) loads, for tool tile i of a block,
-// bytes 64 st + 16 grp of tool row 16 i + qn (the A operand of v_mfma_i32_16x16x64_i8) and reads
-// bytes 64 st + 16 grp of query row 16 sb + qn from LDS (the B operand); its accumulator holds
-// the scores of tools 16 i + 4 grp + r (r = 0..3) for query column 16 sb + qn.
-template <int KT>
-__global__ __launch_bounds__(256, 2) void slb_block_kernel(SlbArgs a) {
+// ---- batches: pass 1.  Workgroup = 64 queries x one range of tools; its 4 waves take 64-tool blocks
+// of the range in turn.  For one block a wave keeps 16 MFMA chains (4 tool tiles x 4 query sub-blocks)
+// and walks the dimension two 64-byte steps at a time, holding those steps of its 64 tool rows in
+// registers (the next two in flight), so every B operand read from LDS feeds four MFMAs.  Lane
+// (qn, grp) loads, for tool tile i of a block, bytes 64 st + 16 grp of tool row 16 i + qn (the A
+// operand) and reads bytes 64 st + 16 grp of query row 16 sb + qn from LDS (the B operand); its
+// accumulator holds the scores of tools 16 i + 4 grp + r (r = 0..3) for query column 16 sb + qn.
+// The best score of each tile (its ordered pattern; 0 for a tile past the registry) goes to
+// part[query][tile].  Keeping a sorted list per lane here instead, a wave inserts nearly every
+// score it meets, because it meets few tools: 65536 tools x 256 queries of dim 768, k 8, whole
+// call: 125 us, this way 47.5 (this pass 34, the second 14).
+__device__ __forceinline__ uint32_t score_order(float score) {
+  const uint32_t u = __float_as_uint(score);
+  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+__device__ __forceinline__ uint32_t umax(uint32_t x, uint32_t y) { return x > y ? x : y; }
+
+__global__ __launch_bounds__(256, 2) void slb_max_kernel(SlbArgs a) {
   constexpr int QB = 64, NT = 4, NSB = 4, CS = 2;   // queries, tool tiles, sub-blocks, steps
   extern __shared__ __align__(16) unsigned char smem[];
   const int dim = a.dim, steps = dim / 64, ld = dim + kQPad;
@@ -318,35 +333,15 @@ __global__ __launch_bounds__(256, 2) void slb_block_kernel(SlbArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qn = lane & 15, grp = lane >> 4;
-  const int q0 = blockIdx.y * QB;
-  const int range = blockIdx.x;
+  // the query blocks of one range sit 8 ids apart: on one XCD, which then reads the range's tools
+  // from memory once
+  const int per8 = 8 * a.n_qblocks;
+  const int id8 = blockIdx.x / per8, in8 = blockIdx.x - id8 * per8;
+  const int range = 8 * id8 + (in8 & 7);
+  const int q0 = (in8 >> 3) * QB;
+  if (range >= a.n_ranges) return;                                       // padding of the grid
   const int t_begin = range * a.range_tools;
-  const int t_end = min(t_begin + a.range_tools, a.n_tools);
-
-  for (int c = tid; c < QB * (dim / 16); c += 256) {
-    const int r = c / (dim / 16), off = (c - r * (dim / 16)) * 16;
-    u32x4 v = u32x4{0u, 0u, 0u, 0u};
-    if (q0 + r < a.n_queries)
-      v = *reinterpret_cast<const u32x4 *>(a.queries + (size_t)(q0 + r) * dim + off);
-    *reinterpret_cast<u32x4 *>(qs + r * ld + off) = v;
-  }
-  for (int i = tid; i < t_end - t_begin; i += 256) tsc[i] = a.tool_scale[t_begin + i];
-  float sq[NSB];
-#pragma unroll
-  for (int sb = 0; sb < NSB; ++sb) {
-    const int q = q0 + 16 * sb + qn;
-    sq[sb] = q < a.n_queries ? a.query_scale[q] : 0.f;
-  }
-  __syncthreads();
-
-  uint64_t best[NSB][KT];
-  uint64_t floor_key[NSB];
-#pragma unroll
-  for (int sb = 0; sb < NSB; ++sb) {
-    floor_key[sb] = 0;
-#pragma unroll
-    for (int j = 0; j < KT; ++j) best[sb][j] = 0;
-  }
+  const int t_end = t_begin + min(a.range_tools, a.n_tools - t_begin);
 
   // this wave's blocks: wave, wave + 4, ... of the range's 64-tool blocks; each is n_chunks
   // chunks of CS steps, walked as one sequence u = block * n_chunks + chunk
@@ -372,6 +367,37 @@ __global__ __launch_bounds__(256, 2) void slb_block_kernel(SlbArgs a) {
         ch.a[i][s2] = *reinterpret_cast<const i32x4 *>(trow + 64 * min(c * CS + s2, steps - 1));
     }
   };
+  Chunk b0, b1;
+  if (total > 0) load_chunk(0, b0);
+
+  // stage the query block: thread tid takes row tid / 4, 16-byte pieces tid % 4, + 4, .. (rows past
+  // the batch are zero); kStageSteps loads at a time in flight
+  {
+    constexpr int kStageSteps = 4;
+    const int r = tid >> 2, q = q0 + r;
+    const int8_t *row = a.queries + (size_t)min(q, a.n_queries - 1) * dim + 16 * (tid & 3);
+    for (int s0 = 0; s0 < steps; s0 += kStageSteps) {
+      u32x4 v[kStageSteps];
+#pragma unroll
+      for (int e = 0; e < kStageSteps; ++e)
+        v[e] = *reinterpret_cast<const u32x4 *>(row + 64 * min(s0 + e, steps - 1));
+#pragma unroll
+      for (int e = 0; e < kStageSteps; ++e)
+        if (s0 + e < steps)
+          *reinterpret_cast<u32x4 *>(qs + r * ld + 64 * (s0 + e) + 16 * (tid & 3)) =
+              q < a.n_queries ? v[e] : u32x4{0u, 0u, 0u, 0u};
+    }
+  }
+  for (int i = tid; i < a.range_tools; i += 256)
+    tsc[i] = t_begin + i < t_end ? a.tool_scale[t_begin + i] : 0.f;
+  float sq[NSB];
+#pragma unroll
+  for (int sb = 0; sb < NSB; ++sb) {
+    const int q = q0 + 16 * sb + qn;
+    sq[sb] = q < a.n_queries ? a.query_scale[q] : 0.f;
+  }
+  __syncthreads();
+
   i32x4 acc[NT][NSB];
   auto step = [&](int u, const Chunk &ch) {
     const int j = u / n_chunks, c = u - j * n_chunks;
@@ -396,34 +422,35 @@ __global__ __launch_bounds__(256, 2) void slb_block_kernel(SlbArgs a) {
       }
     }
     if (c != n_chunks - 1) return;
-    // the candidate pass runs at a raised wave priority, so that its list upkeep interleaves
-    // with the other wave's MFMA chains (about 4% faster at 65536 tools x 256 queries)
-    __builtin_amdgcn_s_setprio(2);
-    // the block's 64 x 64 scores: a candidate that does not beat its column's floor (at most
-    // the column's KT-th best) cannot be among the column's best KT and is dropped
     const int tb = 64 * (wave + kWaves * j);                   // block start within the range
+    uint32_t m[NT][NSB];   // best of the lane's 4 tools of each tile
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
       const f32x4 sc = *reinterpret_cast<const f32x4 *>(tsc + tb + 16 * i + 4 * grp);
+      const int left = t_end - (t_begin + tb + 16 * i + 4 * grp);   // tools the registry still has
 #pragma unroll
       for (int sb = 0; sb < NSB; ++sb) {
+        uint32_t x[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int t = t_begin + tb + 16 * i + 4 * grp + r;
-          const float score = ((float)acc[i][sb][r] * sc[r]) * sq[sb];
-          const uint64_t key = t < t_end ? cand_key(score, t) : 0;
-          insert<KT>(best[sb], key > floor_key[sb] ? key : 0);
-        }
+        for (int r = 0; r < 4; ++r)
+          x[r] = r < left ? score_order(((float)acc[i][sb][r] * sc[r]) * sq[sb]) : 0u;
+        m[i][sb] = umax(umax(x[0], x[1]), umax(x[2], x[3]));
       }
     }
+    // over the column's 4 lanes; lane group grp ends with tile 2 (grp & 1) + (grp >> 1)
+    const int tile = ((t_begin + tb) >> 4) + 2 * (grp & 1) + (grp >> 1);
 #pragma unroll
-    for (int sb = 0; sb < NSB; ++sb) floor_key[sb] = column_floor<KT>(best[sb]);
-    __builtin_amdgcn_s_setprio(0);
+    for (int sb = 0; sb < NSB; ++sb) {
+      const auto p01 = __builtin_amdgcn_permlane32_swap(m[0][sb], m[1][sb], false, false);
+      const auto p23 = __builtin_amdgcn_permlane32_swap(m[2][sb], m[3][sb], false, false);
+      const auto p = __builtin_amdgcn_permlane16_swap(umax(p01[0], p01[1]), umax(p23[0], p23[1]),
+                                                      false, false);
+      const int q = q0 + 16 * sb + qn;
+      if (q < a.n_queries) a.tile_max[(size_t)q * a.tile_ld + tile] = umax(p[0], p[1]);
+    }
   };
   if (total > 0) {
-    Chunk b0, b1;
     int u = 0;
-    load_chunk(0, b0);
     for (;;) {
       load_chunk(u + 1, b1);
       step(u, b0);
@@ -433,54 +460,184 @@ __global__ __launch_bounds__(256, 2) void slb_block_kernel(SlbArgs a) {
       if (++u >= total) break;
     }
   }
+}
 
-  // each column's 4 lists inside the wave, then the 4 waves' lists through LDS
+// ---- batches: pass 2, one workgroup per query.  The KT best tiles: every four threads take the best
+// of their share, the KT-th best of those bounds the KT-th best tile from below, and the tiles at or
+// above it (all in the at most KT quads whose own best reaches it, at most KT of each thread
+// counting) are ranked by counting.  Then one MFMA chain per selected tile scores its tools with the query in
+// every column, and the KT x 16 candidates are ranked by counting.  Latency-bound: a few dependent
+// round trips, with all loads of each in flight together.
+template <int KT>
+__global__ __launch_bounds__(256) void slb_select_kernel(SlbArgs a) {
+  constexpr int kGroups = 64;              // thread quads
+  __shared__ __align__(16) uint64_t keys[16 * KT > kGroups ? 16 * KT : kGroups];
+  __shared__ __align__(16) uint64_t hits[4 * KT * KT];
+  __shared__ uint64_t floor_key;
+  __shared__ uint64_t sorted[KT];
+  __shared__ int sel[KT];
+  __shared__ int n_hits;
+  const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qn = lane & 15, grp = lane >> 4;
+  const int n_tiles = (a.n_tools + 15) / 16;
+  const uint32_t *tm = a.tile_max + (size_t)q * a.tile_ld;     // tile_ld: a multiple of 4
+  // a thread's share: quads of tiles tid, tid + 256, ..; the first kHeld stay in registers
+  constexpr int kHeld = 4;
+  u32x4 held[kHeld];
 #pragma unroll
-  for (int sb = 0; sb < NSB; ++sb) {
-    merge_lanes<KT>(best[sb], 16);
-    merge_lanes<KT>(best[sb], 32);
+  for (int i = 0; i < kHeld; ++i) {
+    const int t = 4 * tid + 1024 * i;
+    held[i] = *reinterpret_cast<const u32x4 *>(tm + (t < a.tile_ld ? t : 0));
   }
-  __syncthreads();                                        // query block and scales no longer read
-  uint64_t *cl = reinterpret_cast<uint64_t *>(smem);      // [wave][NSB][16][KT]
-  if (wave > 0 && grp == 0)
+  if (tid == 0) {
+    floor_key = 0;
+    n_hits = 0;
+  }
+  if (tid < KT) {
+    sorted[tid] = 0;
+    sel[tid] = -1;
+  }
+  // key of a tile: its best score, then the lower tile
+  auto tile_key = [&](uint32_t ord, int t) -> uint64_t {
+    return t < n_tiles ? ((uint64_t)ord << 32) | (0xFFFFFFFFu - (uint32_t)t) : 0;
+  };
+  auto each_tile = [&](auto f) {
 #pragma unroll
-    for (int sb = 0; sb < NSB; ++sb)
+    for (int i = 0; i < kHeld; ++i)
 #pragma unroll
-      for (int j = 0; j < KT; ++j) cl[((wave * NSB + sb) * 16 + qn) * KT + j] = best[sb][j];
-  __syncthreads();
-  if (wave > 0 || grp != 0) return;
+      for (int e = 0; e < 4; ++e) f(tile_key(held[i][e], 4 * tid + 1024 * i + e));
+#pragma unroll 4
+    for (int t = 4 * tid + 1024 * kHeld; t < a.tile_ld; t += 1024) {
+      const u32x4 v = *reinterpret_cast<const u32x4 *>(tm + t);
 #pragma unroll
-  for (int sb = 0; sb < NSB; ++sb) {
-    const int q = q0 + 16 * sb + qn;
-    if (q >= a.n_queries) continue;
-    for (int w = 1; w < kWaves; ++w)
-#pragma unroll
-      for (int j = 0; j < KT; ++j) {
-        uint64_t x = cl[((w * NSB + sb) * 16 + qn) * KT + j];
-#pragma unroll
-        for (int m = 0; m < KT; ++m) {
-          const bool gt = x > best[sb][m];
-          const uint64_t hi = gt ? x : best[sb][m];
-          x = gt ? best[sb][m] : x;
-          best[sb][m] = hi;
-        }
-      }
-    if (a.n_ranges == 1) {
-#pragma unroll
-      for (int j = 0; j < KT; ++j)
-        if (j < a.k) {
-          a.top_idx[(size_t)q * a.k + j] = cand_idx(best[sb][j]);
-          a.top_score[(size_t)q * a.k + j] = cand_score(best[sb][j]);
-        }
-      const float m =
-          best[sb][1] == 0 ? INFINITY : cand_score(best[sb][0]) - cand_score(best[sb][1]);
-      a.margin[q] = m;
-      a.route[q] = m > a.tau ? 1 : 0;
-    } else {
-      const size_t o = ((size_t)q * a.n_ranges + range) * KT;
-#pragma unroll
-      for (int j = 0; j < KT; ++j) a.part[o + j] = best[sb][j];
+      for (int e = 0; e < 4; ++e) f(tile_key(v[e], t + e));
     }
+  };
+  uint64_t mine = 0;
+  each_tile([&](uint64_t key) { mine = key > mine ? key : mine; });
+  uint64_t best4 = mine;                   // of the quad's threads
+#pragma unroll
+  for (int off = 1; off < 4; off <<= 1) {
+    const uint64_t o = shfl_xor_u64(best4, off);
+    best4 = o > best4 ? o : best4;
+  }
+  if ((tid & 3) == 0) keys[tid >> 2] = best4;
+  __syncthreads();
+  auto rank_in = [&](const uint64_t *list, int n, uint64_t key) {
+    int r = 0;
+#pragma unroll 8
+    for (int i = 0; i < n; i += 2) {       // an even number of keys, 16-byte aligned
+      const u32x4 p = *reinterpret_cast<const u32x4 *>(list + i);
+      r += (((uint64_t)p[1] << 32) | p[0]) > key ? 1 : 0;
+      r += (((uint64_t)p[3] << 32) | p[2]) > key ? 1 : 0;
+    }
+    return r;
+  };
+  if (tid < kGroups) {
+    const uint64_t key = keys[tid];
+    if (key != 0 && rank_in(keys, kGroups, key) == KT - 1) floor_key = key;
+  }
+  __syncthreads();
+  const uint64_t fl = floor_key;           // 0: fewer than KT quads have a tile
+  if (mine != 0 && mine >= fl) {
+    uint64_t b[KT];
+#pragma unroll
+    for (int j = 0; j < KT; ++j) b[j] = 0;
+    each_tile([&](uint64_t key) { insert<KT>(b, key >= fl ? key : 0); });
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < KT; ++j) n += b[j] != 0;
+    const int at = atomicAdd(&n_hits, n);  // at most KT quads, 4 threads, KT tiles each
+#pragma unroll
+    for (int j = 0; j < KT; ++j)
+      if (b[j] != 0) hits[at + j] = b[j];
+  }
+  __syncthreads();
+  const int nh = n_hits;
+  if (tid < nh) {                          // nh <= 4 KT KT <= 256
+    const uint64_t key = hits[tid];
+    int r = 0;
+    for (int i = 0; i < nh; ++i) r += hits[i] > key;
+    if (r < KT) sel[r] = (int)(0xFFFFFFFFu - (uint32_t)key);
+  }
+  __syncthreads();
+
+  // ---- tools of the selected tiles: wave w takes places w, w + 4, ..
+  const int dim = a.dim, steps = dim / 64;
+  const float sq = a.query_scale[q];
+  const int8_t *qrow = a.queries + (size_t)q * dim + 16 * grp;
+  constexpr int TW = (KT + kWaves - 1) / kWaves;
+  constexpr int CS = 8;                    // 64-byte steps loaded together
+  int tile[TW];
+  const int8_t *trow[TW];
+#pragma unroll
+  for (int i = 0; i < TW; ++i) {
+    const int place = wave + kWaves * i;
+    tile[i] = place < KT ? sel[place] : -1;
+    trow[i] = a.tools + (size_t)min(16 * max(tile[i], 0) + qn, a.n_tools - 1) * dim + 16 * grp;
+  }
+  if (tile[0] >= 0) {                      // wave-uniform
+    float st[TW];
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+      st[i] = a.tool_scale[min(16 * max(tile[i], 0) + 4 * grp + (qn & 3), a.n_tools - 1)];
+    i32x4 acc[TW];
+#pragma unroll
+    for (int i = 0; i < TW; ++i) acc[i] = i32x4{0, 0, 0, 0};
+    for (int s0 = 0; s0 < steps; s0 += CS) {
+      i32x4 bv[CS], av[TW][CS];
+#pragma unroll
+      for (int e = 0; e < CS; ++e) {       // steps past the end re-read the last one, unused
+        const int off = 64 * min(s0 + e, steps - 1);
+        bv[e] = *reinterpret_cast<const i32x4 *>(qrow + off);
+#pragma unroll
+        for (int i = 0; i < TW; ++i) av[i][e] = *reinterpret_cast<const i32x4 *>(trow[i] + off);
+      }
+#pragma unroll
+      for (int e = 0; e < CS; ++e)
+        if (s0 + e < steps) {
+#pragma unroll
+          for (int i = 0; i < TW; ++i)
+            acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[i][e], bv[e], acc[i], 0, 0, 0);
+        }
+    }
+    // all columns hold the query: lane qn < 4 of a group gives tool 4 grp + qn
+#pragma unroll
+    for (int i = 0; i < TW; ++i) {
+      const int place = wave + kWaves * i;
+      const int t = 16 * tile[i] + 4 * grp + qn;
+      const int dot = qn == 0 ? acc[i][0] : qn == 1 ? acc[i][1] : qn == 2 ? acc[i][2] : acc[i][3];
+      if (qn < 4 && place < KT) {
+        uint64_t key = 0;
+        if (tile[i] >= 0 && t < a.n_tools)
+          key = cand_key(((float)dot * st[i]) * sq, t);
+        keys[16 * place + 4 * grp + qn] = key;
+      }
+    }
+  } else if (lane < 16) {
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+      if (wave + kWaves * i < KT) keys[16 * (wave + kWaves * i) + lane] = 0;
+  }
+  __syncthreads();
+  if (tid < 16 * KT) {
+    const uint64_t key = keys[tid];
+    if (key != 0) {
+      const int r = rank_in(keys, 16 * KT, key);
+      if (r < KT) sorted[r] = key;
+    }
+  }
+  __syncthreads();
+  if (tid < a.k) {
+    a.top_idx[(size_t)q * a.k + tid] = cand_idx(sorted[tid]);
+    a.top_score[(size_t)q * a.k + tid] = cand_score(sorted[tid]);
+  }
+  if (tid == 0) {
+    // fewer than two tools: nothing to confuse the best one with
+    const float m = sorted[1] == 0 ? INFINITY : cand_score(sorted[0]) - cand_score(sorted[1]);
+    a.margin[q] = m;
+    a.route[q] = m > a.tau ? 1 : 0;
   }
 }
 
@@ -495,67 +652,100 @@ __global__ __launch_bounds__(64) void slb_merge_kernel(SlbArgs a) {
 
 // Symmetric per-row INT8 quantisation: one wave per row; scale = max |x| / 127, code =
 // x / scale rounded to nearest-even (IEEE fp32 division), |code| <= 127; a zero row gets scale 0.
+__device__ __forceinline__ int quant_code(float x, float s) {
+  const float c = s > 0.f ? rintf(x / s) : 0.f;
+  return (int)fminf(fmaxf(c, -127.f), 127.f);
+}
+// QUADS: rows of up to 1024 features in whole, aligned float4s: the row is read once, all its loads
+// in flight together, and stays in registers; else two passes, a feature per lane at a time.  The
+// loads' latency bounds a small batch: 256 rows of 768: 8.4 -> 4.2 us; a registry of
+// 65536 rows: 126 -> 52 us.
+template <bool QUADS>
 __global__ __launch_bounds__(256) void slb_quantize_kernel(const float *x, int32_t n, int32_t dim,
                                                            int8_t *q, float *scale) {
+  constexpr int NV = 4;                    // float4s a lane holds
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= n) return;
   const float *xr = x + (size_t)row * dim;
+  int8_t *qr = q + (size_t)row * dim;
   float m = 0.f;
-  for (int j = lane; j < dim; j += 64) m = fmaxf(m, fabsf(xr[j]));
+  f32x4 v[NV];
+  if constexpr (QUADS) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int j = 4 * (lane + 64 * i);
+      v[i] = j < dim ? *reinterpret_cast<const f32x4 *>(xr + j) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m = fmaxf(m, fabsf(v[i][e]));
+  } else {
+    for (int j = lane; j < dim; j += 64) m = fmaxf(m, fabsf(xr[j]));
+  }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
   const float s = m / 127.0f;
   if (lane == 0) scale[row] = s;
-  int8_t *qr = q + (size_t)row * dim;
-  for (int j = lane; j < dim; j += 64) {
-    float c = s > 0.f ? rintf(xr[j] / s) : 0.f;
-    c = fminf(fmaxf(c, -127.f), 127.f);
-    qr[j] = (int8_t)(int)c;
+  if constexpr (QUADS) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int j = 4 * (lane + 64 * i);
+      if (j >= dim) break;
+      uint32_t w = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w |= (uint32_t)(quant_code(v[i][e], s) & 0xff) << (8 * e);
+      *reinterpret_cast<uint32_t *>(qr + j) = w;
+    }
+  } else {
+    for (int j = lane; j < dim; j += 64) qr[j] = (int8_t)quant_code(xr[j], s);
   }
 }
 
 }  // namespace
 
 namespace {
-// More queries than this take the batched kernel (from two 16-query sub-blocks on, a tool row
-// read feeds more than one query column).
+// More queries than this take the batched kernels (from two 16-query sub-blocks on, a tool row
+// read feeds more than one query column), if the registry is larger than one range of the small
+// scan, which then needs no second launch and no workspace.
 constexpr int kBlockMinQueries = 16;
+constexpr int32_t kOneRangeTools = 256;
+constexpr int kBlockQueries = 16 * kSubBlocks;
 constexpr int64_t kBlockWgs = 512;        // batched kernel: two resident workgroups per CU
 constexpr int64_t kBlockMaxRange = 32;    // 64-tool blocks per range (its scales sit in LDS)
+// Tile maxima of one pass over the registry: the batch goes in chunks of whole query blocks that
+// stay within this (a registry of a million tools takes 256 queries a pass).
+constexpr int64_t kTileMaxBytes = (int64_t)64 << 20;
 
-bool batched(int32_t n_queries) { return n_queries > kBlockMinQueries; }
-
-size_t block_lds_bytes(int32_t dim, int32_t range_tools) {
-  const size_t stage = (size_t)64 * (dim + kQPad) + (size_t)range_tools * sizeof(float);
-  const size_t merge = (size_t)kWaves * kSubBlocks * 16 * kTop * 8;
-  return stage > merge ? stage : merge;
+bool batched(int32_t n_tools, int32_t n_queries) {
+  return n_queries > kBlockMinQueries && n_tools > kOneRangeTools;
+}
+int64_t tile_ld_of(int32_t n_tools) { return ((int64_t)n_tools + 63) / 64 * 4; }
+int32_t chunk_queries(int32_t n_tools, int32_t n_queries) {
+  const int64_t fit = kTileMaxBytes / (tile_ld_of(n_tools) * 4) / kBlockQueries * kBlockQueries;
+  const int64_t c = fit < kBlockQueries ? kBlockQueries : fit;
+  return (int32_t)(c < n_queries ? c : n_queries);
+}
+// Tools per range of a batched pass: about kBlockWgs workgroups, 4 to kBlockMaxRange 64-tool
+// blocks per range (at least one block per wave).
+int32_t block_range_tools(int32_t n_tools, int32_t n_queries) {
+  const int64_t q_blocks = ((int64_t)n_queries + kBlockQueries - 1) / kBlockQueries;
+  const int64_t blocks = ((int64_t)n_tools + 63) / 64;
+  int64_t per = (blocks * q_blocks + kBlockWgs - 1) / kBlockWgs;
+  if (per < 4) per = 4;
+  if (per > kBlockMaxRange) per = kBlockMaxRange;
+  return (int32_t)(per * 64);
 }
 }  // namespace
 
 void slb_geometry(int32_t n_tools, int32_t n_queries, int32_t dim, int32_t &n_ranges,
                   int32_t &range_tools) {
   (void)dim;
-  const int qb = 16 * kSubBlocks;
-  if (batched(n_queries)) {
-    // about kBlockWgs workgroups, 4 to kBlockMaxRange 64-tool blocks per range (at least one
-    // block per wave)
-    const int64_t q_blocks = ((int64_t)n_queries + qb - 1) / qb;
-    const int64_t blocks = ((int64_t)n_tools + 63) / 64;
-    int64_t per = (blocks * q_blocks + kBlockWgs - 1) / kBlockWgs;
-    if (per < 4) per = 4;
-    if (per > kBlockMaxRange) per = kBlockMaxRange;
-    range_tools = (int32_t)(per * 64);
-    n_ranges = (int32_t)(((int64_t)n_tools + range_tools - 1) / range_tools);
-    return;
-  }
-  const int64_t q_blocks = ((int64_t)n_queries + qb - 1) / qb;
+  (void)n_queries;
   const int64_t tiles = ((int64_t)n_tools + 63) / 64;                 // 64-tool units
-  // about 1024 workgroups, at least 256 tools per range, at most 256 ranges (the merge reads
-  // 8 candidates of each)
-  int64_t nr = (1024 + q_blocks - 1) / q_blocks;
-  const int64_t max_nr = (tiles + 3) / 4;
-  if (nr > max_nr) nr = max_nr;
+  // at least 256 tools per range, at most 256 ranges (the merge reads 8 candidates of each)
+  int64_t nr = (tiles + 3) / 4;
   if (nr > 256) nr = 256;
   if (nr < 1) nr = 1;
   const int64_t per = (tiles + nr - 1) / nr;
@@ -564,6 +754,8 @@ void slb_geometry(int32_t n_tools, int32_t n_queries, int32_t dim, int32_t &n_ra
 }
 
 size_t slb_workspace_bytes(int32_t n_tools, int32_t n_queries, int32_t dim) {
+  if (batched(n_tools, n_queries))
+    return (size_t)chunk_queries(n_tools, n_queries) * tile_ld_of(n_tools) * sizeof(uint32_t);
   int32_t nr, rt;
   slb_geometry(n_tools, n_queries, dim, nr, rt);
   if (nr <= 1) return 0;
@@ -572,8 +764,13 @@ size_t slb_workspace_bytes(int32_t n_tools, int32_t n_queries, int32_t dim) {
 
 hipError_t launch_slb_quantize(const float *x, int32_t n, int32_t dim, int8_t *q, float *scale,
                                hipStream_t stream) {
-  hipLaunchKernelGGL(slb_quantize_kernel, dim3((n + 3) / 4), dim3(256), 0, stream, x, n, dim, q,
-                     scale);
+  const bool quads = dim % 4 == 0 && dim <= 1024 && (uintptr_t)x % 16 == 0 && (uintptr_t)q % 4 == 0;
+  if (quads)
+    hipLaunchKernelGGL(slb_quantize_kernel<true>, dim3((n + 3) / 4), dim3(256), 0, stream, x, n, dim,
+                       q, scale);
+  else
+    hipLaunchKernelGGL(slb_quantize_kernel<false>, dim3((n + 3) / 4), dim3(256), 0, stream, x, n, dim,
+                       q, scale);
   return hipGetLastError();
 }
 
@@ -592,33 +789,45 @@ hipError_t launch_slb_scan(const SlbLaunch &p, hipStream_t stream) {
   a.top_score = p.top_score;
   a.margin = p.margin;
   a.route = p.route;
-  slb_geometry(p.n_tools, p.n_queries, p.dim, a.n_ranges, a.range_tools);
-  if (a.n_ranges > 1) a.part = reinterpret_cast<uint64_t *>(p.workspace);
-  const int qb = 16 * kSubBlocks;
-  const dim3 grid(a.n_ranges, (p.n_queries + qb - 1) / qb);
   const int kt = p.k <= 2 ? 2 : p.k <= 4 ? 4 : 8;
-  if (batched(p.n_queries)) {
-    const size_t lds = block_lds_bytes(p.dim, a.range_tools);
-    auto run = [&](auto kernel) -> hipError_t {
+  if (batched(p.n_tools, p.n_queries)) {
+    a.tile_max = reinterpret_cast<uint32_t *>(p.workspace);
+    a.tile_ld = (int32_t)tile_ld_of(p.n_tools);
+    const int32_t chunk = chunk_queries(p.n_tools, p.n_queries);
+    for (int32_t q0 = 0; q0 < p.n_queries; q0 += chunk) {
+      a.n_queries = p.n_queries - q0 < chunk ? p.n_queries - q0 : chunk;
+      a.queries = p.queries + (size_t)q0 * p.dim;
+      a.query_scale = p.query_scale + q0;
+      a.top_idx = p.top_idx + (size_t)q0 * p.k;
+      a.top_score = p.top_score + (size_t)q0 * p.k;
+      a.margin = p.margin + q0;
+      a.route = p.route + q0;
+      a.n_qblocks = (a.n_queries + kBlockQueries - 1) / kBlockQueries;
+      a.range_tools = block_range_tools(p.n_tools, a.n_queries);
+      a.n_ranges = (int32_t)(((int64_t)p.n_tools + a.range_tools - 1) / a.range_tools);
+      const size_t lds = (size_t)kBlockQueries * (p.dim + kQPad) +
+                         (size_t)a.range_tools * sizeof(float);
       if (lds > 65536) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(slb_max_kernel),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  (int)lds);
         if (e != hipSuccess) return e;
       }
-      hipLaunchKernelGGL(kernel, grid, dim3(256), lds, stream, a);
-      return hipGetLastError();
-    };
-    hipError_t e = kt == 2 ? run(slb_block_kernel<2>)
-                   : kt == 4 ? run(slb_block_kernel<4>)
-                             : run(slb_block_kernel<8>);
-    if (e != hipSuccess || a.n_ranges <= 1) return e;
-    if (kt == 2) hipLaunchKernelGGL(slb_merge_kernel<2>, dim3(p.n_queries), dim3(64), 0, stream, a);
-    else if (kt == 4) hipLaunchKernelGGL(slb_merge_kernel<4>, dim3(p.n_queries), dim3(64), 0, stream, a);
-    else hipLaunchKernelGGL(slb_merge_kernel<8>, dim3(p.n_queries), dim3(64), 0, stream, a);
-    return hipGetLastError();
+      const uint32_t wgs = (uint32_t)((a.n_ranges + 7) / 8 * 8) * (uint32_t)a.n_qblocks;
+      hipLaunchKernelGGL(slb_max_kernel, dim3(wgs), dim3(256), lds, stream, a);
+      const dim3 sgrid(a.n_queries);
+      if (kt == 2) hipLaunchKernelGGL(slb_select_kernel<2>, sgrid, dim3(256), 0, stream, a);
+      else if (kt == 4) hipLaunchKernelGGL(slb_select_kernel<4>, sgrid, dim3(256), 0, stream, a);
+      else hipLaunchKernelGGL(slb_select_kernel<8>, sgrid, dim3(256), 0, stream, a);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
-  // at most 16 queries: one query block
+  slb_geometry(p.n_tools, p.n_queries, p.dim, a.n_ranges, a.range_tools);
+  if (a.n_ranges > 1) a.part = reinterpret_cast<uint64_t *>(p.workspace);
+  // one 16-query block, or several over a registry of one range
+  const dim3 grid(a.n_ranges > 1 ? a.n_ranges : (p.n_queries + 15) / 16);
   const size_t stage = (size_t)16 * (p.dim + kQPad);
   const size_t merge = (size_t)kWaves * 16 * kTop * 8;
   const size_t lds = stage > merge ? stage : merge;

@@ -4,10 +4,12 @@
 // [l][page][h][slot][:] are contiguous, so the row-major kernel streams 16-byte chunks in the
 // block's own order (coalesced reads) and writes whole rows (256 B for bf16, head_dim 128),
 // both with non-temporal accesses (config 3, 48 layers, steady state: 70.6 -> 64.6 us).
-// The transposed-V kernel stages a 64-token x head_dim tile in LDS and writes it back
-// token-innermost, so both the row reads and the column writes stay coalesced.
+// The transposed-V kernel transposes 16-byte x 16-byte blocks in registers: whole rows are read, and
+// every feature row of the cache is written a page (32 or 64 bytes) at a time.
 #include "device_common.h"
 #include "launch.h"
+
+#include <algorithm>
 
 namespace nexus {
 
@@ -56,64 +58,64 @@ __global__ __launch_bounds__(256) void splice_rows_kernel(
   (void)n_tokens;
 }
 
-// Transposed-V splice.  One workgroup = (layer, head, 64-token window aligned to logical
-// pages).  Block V rows for the window are read into LDS, then every head_dim row of the
-// cache receives the window's tokens as 8-token (16-byte) column pieces.  Only tokens inside
-// [offset, offset + n_tokens) are written.  Element type is 16-bit (bf16) or 32-bit (f32).
+// Transposed-V splice.  A thread takes an E x E block (E = 16 bytes of elements: 8 bf16, 4 f32): E
+// tokens of one logical page, one 16-byte chunk of features.  It loads the chunk from E block rows,
+// all in flight together, and stores E tokens to each of the E feature rows; the 16 / E blocks of a
+// page sit in adjacent lanes, so a page is one 32- or 64-byte piece of a feature row.  Only tokens
+// inside [offset, offset + n_tokens) are written.
+// The pieces bound it: where logical pages are neighbours in memory, pieces of several pages make up
+// a cache line, so all pages of a (layer, head) go to one XCD (ids 8 apart), whose L2 joins them.
+// 26 layers x 512 tokens x 8 heads of 256 bf16, shuffled pages, cold caches: 76 us (through an LDS
+// tile, a head's pages over all XCDs) -> 55 us.
 template <typename T>
 __global__ __launch_bounds__(256) void splice_vt_kernel(
     const T *__restrict__ bv, T *__restrict__ cvt, const int32_t *__restrict__ map,
-    int64_t offset, int32_t n_tokens, int32_t n_heads, int32_t head_dim, int32_t n_phys_pages,
-    int64_t first_window_start) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  T *tile = reinterpret_cast<T *>(smem_raw);  // [64][head_dim + pad]
-  const int pad = 16 / (int)sizeof(T);
-  const int ld = head_dim + pad;
-  const int layer = blockIdx.z;
-  const int h = blockIdx.y;
-  const int64_t w0 = first_window_start + (int64_t)blockIdx.x * 64;  // logical, page aligned
-  // stage: tokens t in [w0, w0 + 64) that belong to the block
-  const int epc = 16 / (int)sizeof(T);           // elements per 16-byte chunk
-  const int cpr = head_dim / epc;                // chunks per row
-  for (int u = threadIdx.x; u < 64 * cpr; u += blockDim.x) {
-    const int tt = u / cpr, c = u - tt * cpr;
-    const int64_t t = w0 + tt;
-    if (t < offset || t >= offset + n_tokens) continue;
-    const int64_t j = t - offset;
-    const uint4 val = *reinterpret_cast<const uint4 *>(
-        bv + (((int64_t)layer * n_tokens + j) * n_heads + h) * head_dim + (int64_t)c * epc);
-    *reinterpret_cast<uint4 *>(tile + tt * ld + c * epc) = val;
+    int64_t offset, int32_t n_tokens, int32_t n_heads, int32_t head_dim, uint32_t chunk_shift,
+    int32_t n_phys_pages, int32_t n_pages, uint32_t n_groups, uint32_t first_group) {
+  constexpr int E = 16 / (int)sizeof(T);
+  constexpr int PB = kPage / E;                       // blocks per page and chunk
+  const uint32_t group = first_group + 8 * blockIdx.y + (blockIdx.x & 7);   // layer * n_heads + head
+  if (group >= n_groups) return;                      // padding of the grid
+  const uint32_t item = (blockIdx.x >> 3) * 256 + threadIdx.x;
+  const int g = item % PB;
+  const int c = (item / PB) & ((1u << chunk_shift) - 1);
+  const int p = (int)(item / PB >> chunk_shift);
+  if (p >= n_pages) return;
+  const int64_t page0 = offset >> kPageShift;
+  const int64_t t0 = (page0 + p) * kPage + g * E, t_end = offset + n_tokens;
+  if (t0 + E <= offset || t0 >= t_end) return;        // no block token here
+  const uint32_t layer = group / (uint32_t)n_heads, h = group - layer * n_heads;
+  const int64_t phys = (uint32_t)map[page0 + p];
+  const T *src = bv + ((int64_t)layer * n_tokens * n_heads + h) * head_dim + c * E;
+  const int64_t row = (int64_t)n_heads * head_dim;
+  u32x4 v[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int64_t t = t0 + e < offset ? offset : t0 + e < t_end ? t0 + e : t_end - 1;
+    v[e] = ld_stream(reinterpret_cast<const u32x4 *>(src + (t - offset) * row));
   }
-  __syncthreads();
-  // write: for each d, 8 groups of 8 tokens
   const int64_t n_cols = (int64_t)n_phys_pages * kPage;
-  T *base = cvt + ((int64_t)layer * n_heads + h) * head_dim * n_cols;
-  for (int u = threadIdx.x; u < head_dim * 8; u += blockDim.x) {
-    const int d = u >> 3, grp = u & 7;
-    const int64_t t0 = w0 + grp * 8;
-    if (t0 + 8 <= offset || t0 >= offset + n_tokens) continue;  // no block token in this group
-    const int64_t page = map[t0 >> kPageShift];
-    T *dst = base + (int64_t)d * n_cols + page * kPage + (t0 & (kPage - 1));
-    const T *col = tile + (grp * 8) * ld + d;
-    if (t0 >= offset && t0 + 8 <= offset + n_tokens) {
-      if (sizeof(T) == 2) {
-        uint4 w;
-        w.x = (uint32_t)col[0 * ld] | ((uint32_t)col[1 * ld] << 16);
-        w.y = (uint32_t)col[2 * ld] | ((uint32_t)col[3 * ld] << 16);
-        w.z = (uint32_t)col[4 * ld] | ((uint32_t)col[5 * ld] << 16);
-        w.w = (uint32_t)col[6 * ld] | ((uint32_t)col[7 * ld] << 16);
-        *reinterpret_cast<uint4 *>(dst) = w;
-      } else {
-        uint4 w0v, w1v;
-        w0v.x = col[0 * ld]; w0v.y = col[1 * ld]; w0v.z = col[2 * ld]; w0v.w = col[3 * ld];
-        w1v.x = col[4 * ld]; w1v.y = col[5 * ld]; w1v.z = col[6 * ld]; w1v.w = col[7 * ld];
-        reinterpret_cast<uint4 *>(dst)[0] = w0v;
-        reinterpret_cast<uint4 *>(dst)[1] = w1v;
-      }
+  T *dst = cvt + ((int64_t)group * head_dim + c * E) * n_cols + phys * kPage + g * E;
+  const bool whole = t0 >= offset && t0 + E <= t_end;
+#pragma unroll
+  for (int d = 0; d < E; ++d) {
+    u32x4 w;
+    if constexpr (sizeof(T) == 2) {
+      const uint32_t sel = (d & 1) ? 0x07060302u : 0x05040100u;   // high or low halves
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        w[i] = __builtin_amdgcn_perm(v[2 * i + 1][d >> 1], v[2 * i][d >> 1], sel);
     } else {
-      for (int e = 0; e < 8; ++e) {
-        const int64_t t = t0 + e;
-        if (t >= offset && t < offset + n_tokens) dst[e] = col[e * ld];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[i] = v[i][d];
+    }
+    if (whole) {
+      *reinterpret_cast<u32x4 *>(dst + d * n_cols) = w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const T x = sizeof(T) == 2 ? (T)(w[e * sizeof(T) / 4] >> (16 * (e & 1))) : (T)w[e & 3];
+        if (t0 + e >= offset && t0 + e < t_end) dst[d * n_cols + e] = x;
       }
     }
   }
@@ -140,20 +142,24 @@ hipError_t launch_splice(const SpliceLaunch &p, hipStream_t stream) {
     if (e != hipSuccess) return e;
   }
   if (p.v_transposed) {
-    const int64_t w_first = (p.offset / 64) * 64;
-    const int64_t w_last = (p.offset + p.n_tokens - 1) / 64;
-    const uint32_t n_windows = (uint32_t)(w_last - p.offset / 64 + 1);
-    dim3 grid(n_windows, p.n_heads, p.n_layers);
-    const int pad = 16 / (int)esize;
-    const size_t smem = (size_t)64 * (p.head_dim + pad) * esize;
-    if (esize == 2)
-      hipLaunchKernelGGL(splice_vt_kernel<uint16_t>, grid, dim3(256), smem, stream,
-                         (const uint16_t *)p.block_v, (uint16_t *)p.cache_v, p.map, p.offset,
-                         p.n_tokens, p.n_heads, p.head_dim, p.n_phys_pages, w_first);
-    else
-      hipLaunchKernelGGL(splice_vt_kernel<uint32_t>, grid, dim3(256), smem, stream,
-                         (const uint32_t *)p.block_v, (uint32_t *)p.cache_v, p.map, p.offset,
-                         p.n_tokens, p.n_heads, p.head_dim, p.n_phys_pages, w_first);
+    // transposed rows of up to 1008 bytes, the entry points' limit (head_dim 252 in f32)
+    if (64u * ((uint32_t)p.head_dim * esize + 16u) > 65536u) return hipErrorInvalidValue;
+    const int32_t n_pages = (int32_t)(((p.offset + p.n_tokens - 1) >> kPageShift) -
+                                      (p.offset >> kPageShift) + 1);
+    const uint32_t n_groups = (uint32_t)p.n_layers * (uint32_t)p.n_heads;
+    const uint64_t blocks = (uint64_t)n_pages * chunks_per_row * (kPage * esize / 16);
+    const uint32_t wpg = (uint32_t)((blocks + 255) / 256);
+    // grid y: 8 groups each (at most 65535 of them to a launch), x: their workgroups in turn
+    for (uint32_t g0 = 0; g0 < n_groups; g0 += 8 * 65535u) {
+      const dim3 grid(8 * wpg, std::min<uint32_t>((n_groups - g0 + 7) / 8, 65535u));
+#define NEXUS_SPLICE_VT(T)                                                                          \
+  hipLaunchKernelGGL(splice_vt_kernel<T>, grid, dim3(256), 0, stream, (const T *)p.block_v,         \
+                     (T *)p.cache_v, p.map, p.offset, p.n_tokens, p.n_heads, p.head_dim, shift,     \
+                     p.n_phys_pages, n_pages, n_groups, g0)
+      if (esize == 2) NEXUS_SPLICE_VT(uint16_t);
+      else NEXUS_SPLICE_VT(uint32_t);
+#undef NEXUS_SPLICE_VT
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

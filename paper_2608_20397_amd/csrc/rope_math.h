@@ -14,9 +14,10 @@ constexpr int kMaxPairs = 512;                            // head_dim <= 1024
 
 // cos and sin of delta * theta_i, theta_i = base^(-2i/D): the angle is formed and reduced
 // modulo 2 pi in fp64 (two-term 2 pi), then sincos in fp64.
-__device__ __forceinline__ void pair_angle(int64_t delta, double base, int i, int head_dim,
-                                           double &c, double &s) {
-  const double theta = pow(base, -2.0 * (double)i / (double)head_dim);
+__device__ __forceinline__ double pair_theta(double base, int i, int head_dim) {
+  return pow(base, -2.0 * (double)i / (double)head_dim);
+}
+__device__ __forceinline__ void pair_angle(int64_t delta, double theta, double &c, double &s) {
   const double ang = (double)delta * theta;
   const double k = rint(ang / kTwoPiHi);
   double r = fma(-k, kTwoPiHi, ang);
@@ -105,14 +106,19 @@ inline void rope_tab_host(int64_t delta, double base, int head_dim, RopeTab &t) 
 }
 
 // fp32 head + tail of the cosine and sine of pair i at angle delta * theta_i
-__device__ __forceinline__ void pair_cs(int64_t delta, double base, int i, int head_dim,
-                                        float &ch, float &cl, float &sh, float &sl) {
+__device__ __forceinline__ void pair_cs_theta(int64_t delta, double theta, float &ch, float &cl,
+                                              float &sh, float &sl) {
   double c, s;
-  pair_angle(delta, base, i, head_dim, c, s);
+  pair_angle(delta, theta, c, s);
   ch = (float)c;
   cl = (float)(c - (double)ch);
   sh = (float)s;
   sl = (float)(s - (double)sh);
+}
+
+__device__ __forceinline__ void pair_cs(int64_t delta, double base, int i, int head_dim,
+                                        float &ch, float &cl, float &sh, float &sl) {
+  pair_cs_theta(delta, pair_theta(base, i, head_dim), ch, cl, sh, sl);
 }
 
 }  // namespace nexus

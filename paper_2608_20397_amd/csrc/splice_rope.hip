@@ -43,10 +43,11 @@ __global__ __launch_bounds__(256) void rope_splice_kernel(
     int32_t n_phys_pages, int64_t angle0, double base, const RopeTab tab) {
   constexpr int N = Pack<T>::N;
   __shared__ float cs_tab[4][PER_TOKEN ? kTileTokens : 1][kMaxPairsTab];
-  // With the host's table the single-rotation instance needs 62 registers, so 8 of its
-  // workgroups would share a CU; at 8 it ran 3% slower than at the 4 its fp64 angle code allowed
-  // (config 3 shapes, 48 layers: 5.88 against 6.05 TB/s).  It reserves LDS so that 4 fit.
-  __shared__ float occ_cap[PER_TOKEN ? 1 : kOccCapFloats];
+  // By its registers 7 or 8 workgroups would share a CU; at that the single-rotation instance ran 3%
+  // slower than at 4 (config 3 shapes, 48 layers: 5.88 against 6.05 TB/s), the per-token one 2%
+  // (rope-append of 1024 tokens x 48 layers: 71.4 against 69.8 us).
+  // LDS is reserved so that 4 fit.
+  __shared__ float occ_cap[PER_TOKEN ? kOccCapFloats - 3 * 4 * kMaxPairsTab : kOccCapFloats];
   if (threadIdx.x >= blockDim.x) occ_cap[0] = 0.f;   // keeps the reservation
   const int j0 = blockIdx.x * kTileTokens;
   const int l = blockIdx.y;
@@ -89,12 +90,14 @@ __global__ __launch_bounds__(256) void rope_splice_kernel(
   for (int u = 0; u < kBatch; ++u) load(threadIdx.x + u * blockDim.x, cur[u]);
 
   if constexpr (PER_TOKEN) {
-    // token j0 + t sits at angle0 + j0 + t
-    for (int x = threadIdx.x; x < n_tok * n_pairs; x += blockDim.x) {
-      const int t = x / n_pairs, i = x - t * n_pairs;
-      pair_cs(angle0 + j0 + t, base, i, head_dim, cs_tab[0][t][i], cs_tab[1][t][i],
-              cs_tab[2][t][i], cs_tab[3][t][i]);
-    }
+    // token j0 + t sits at angle0 + j0 + t; a thread keeps its pair (n_pairs is a power of two), so
+    // the pair's frequency is formed once
+    const int i = threadIdx.x & (n_pairs - 1);
+    const int step = blockDim.x / n_pairs;
+    const double theta = pair_theta(base, i, head_dim);
+    for (int t = threadIdx.x / n_pairs; t < n_tok; t += step)
+      pair_cs_theta(angle0 + j0 + t, theta, cs_tab[0][t][i], cs_tab[1][t][i], cs_tab[2][t][i],
+                    cs_tab[3][t][i]);
   } else {
     // every token turns by angle0
     for (int i = threadIdx.x; i < n_pairs; i += blockDim.x) {

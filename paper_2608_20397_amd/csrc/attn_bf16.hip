@@ -456,6 +456,7 @@ struct KernelShape {
 
 KernelShape kernel_shape(const AttnLaunch &p) {
   if (p.head_dim == 128 && !p.v_transposed) return {kQB, 64, 2, kWaves, 0.03};   // LDS DMA
+  if (p.head_dim == 64 && !p.v_transposed) return {kQB, 64, 3, kWaves, 0.015};   // LDS DMA
   if (p.head_dim == 256 && p.v_transposed) return {kQB, 32, 1, kWavesWide, 0.04};   // LDS DMA
   return {kQB, key_tile_for(p.head_dim), p.head_dim >= 256 ? 1 : 2, kWaves,
           0.03 * p.head_dim / 128.0};
@@ -738,29 +739,22 @@ bool make_plan(const AttnLaunch &p, AttnPlan &plan) {
   return true;
 }
 
-template <int D, int KT, bool VT, bool CAP>
-void launch_main(const AttnArgs &args, const AttnPlan &plan, int n_kv, hipStream_t stream) {
-  hipLaunchKernelGGL((attn_bf16_kernel<D, KT, VT, CAP>), dim3(plan.units_per_head * n_kv),
-                     dim3(256), 0, stream, args, plan);
-}
-
-template <int D, int KT>
-void dispatch_main(const AttnArgs &args, const AttnPlan &plan, int n_kv, bool vt, bool cap,
-                   hipStream_t stream) {
-  if (vt) {
-    if (cap) launch_main<D, KT, true, true>(args, plan, n_kv, stream);
-    else launch_main<D, KT, true, false>(args, plan, n_kv, stream);
-  } else {
-    if (cap) launch_main<D, KT, false, true>(args, plan, n_kv, stream);
-    else launch_main<D, KT, false, false>(args, plan, n_kv, stream);
-  }
+template <int D, int KT, bool VT>
+hipError_t launch_main(const AttnArgs &args, const AttnPlan &plan, int n_kv, bool cap,
+                       hipStream_t stream) {
+  const dim3 grid(plan.units_per_head * n_kv);
+  if (cap)
+    hipLaunchKernelGGL((attn_bf16_kernel<D, KT, VT, true>), grid, dim3(256), 0, stream, args, plan);
+  else
+    hipLaunchKernelGGL((attn_bf16_kernel<D, KT, VT, false>), grid, dim3(256), 0, stream, args, plan);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_attention_f32(const AttnLaunch &p, hipStream_t stream);
-hipError_t launch_attn_d128_dma(const AttnArgs &args, const AttnPlan &plan, int n_kv, bool cap,
-                                hipStream_t stream);
+hipError_t launch_attn_dma(const AttnArgs &args, const AttnPlan &plan, int head_dim, int n_kv,
+                           bool cap, hipStream_t stream);
 hipError_t launch_attn_d256_vt(const AttnArgs &args, const AttnPlan &plan, int n_kv, bool cap,
                                hipStream_t stream);
 
@@ -794,27 +788,18 @@ hipError_t launch_attention(const AttnLaunch &p, hipStream_t stream) {
   args.cap_out = p.softcap * log2e;
   args.cap_k = p.softcap > 0.f ? 2.0f * p.scale * log2e / p.softcap : 0.f;
   const bool cap = p.softcap > 0.f;
-  switch (p.head_dim) {
-    case 64: dispatch_main<64, 64>(args, plan, p.n_kv_heads, p.v_transposed, cap, stream); break;
-    case 128:
-      if (!p.v_transposed) {
-        const hipError_t e = launch_attn_d128_dma(args, plan, p.n_kv_heads, cap, stream);
-        if (e != hipSuccess) return e;
-      } else {
-        dispatch_main<128, 64>(args, plan, p.n_kv_heads, p.v_transposed, cap, stream);
-      }
-      break;
-    case 256:
-      if (p.v_transposed) {
-        const hipError_t e = launch_attn_d256_vt(args, plan, p.n_kv_heads, cap, stream);
-        if (e != hipSuccess) return e;
-      } else {
-        dispatch_main<256, 32>(args, plan, p.n_kv_heads, p.v_transposed, cap, stream);
-      }
-      break;
-    default: return hipErrorInvalidValue;
-  }
-  hipError_t e = hipGetLastError();
+  const bool vt = p.v_transposed;
+  hipError_t e = hipSuccess;
+  if (p.head_dim <= 128 && !vt)
+    e = launch_attn_dma(args, plan, p.head_dim, p.n_kv_heads, cap, stream);
+  else if (p.head_dim == 64)
+    e = launch_main<64, 64, true>(args, plan, p.n_kv_heads, cap, stream);
+  else if (p.head_dim == 128)
+    e = launch_main<128, 64, true>(args, plan, p.n_kv_heads, cap, stream);
+  else if (vt)
+    e = launch_attn_d256_vt(args, plan, p.n_kv_heads, cap, stream);
+  else
+    e = launch_main<256, 32, false>(args, plan, p.n_kv_heads, cap, stream);
   if (e != hipSuccess) return e;
   if (plan.any_split) {
     const int64_t total = (int64_t)plan.total_rows * p.n_q_heads * (p.head_dim / 16);

@@ -1,5 +1,5 @@
-// bf16 suffix attention, head_dim 128 with a row-major V cache: the variant that feeds LDS with
-// gfx950's LDS DMA loads (Sec. III-A; the re-decoded suffix of Sec. VI-A).
+// bf16 suffix attention, head_dim 64 and 128 with a row-major V cache: the variant that feeds LDS
+// with gfx950's LDS DMA loads (Sec. III-A; the re-decoded suffix of Sec. VI-A).
 //
 // Same work decomposition and math as attn_bf16_kernel (one KV head per workgroup, 4 waves, each
 // wave one query head x 32 queries, S^T = K.Q^T and O^T += V^T.P^T on 32x32x16 MFMA, online
@@ -18,9 +18,16 @@
 //     V[key_e][d0 + 4q], so output lane i receives V[key_0..3][d0 + i].  The keys each lane
 //     needs follow the score layout of the S^T MFMA (keys 4h..4h+3 and 8+4h..8+4h+3 of a
 //     16-key step for lane half h).
-// LDS tiles: K row r (256 B) holds chunk c at c ^ (r & 15); V row r holds chunk c at
-// c ^ 4 (r & 3).  Both keep the 16-byte K reads and the 8-byte transposed V reads of a wave free
-// of bank conflicts.
+// LDS tiles, head_dim 128: K row r (256 B) holds chunk c at c ^ (r & 15); V row r holds chunk c at
+// c ^ 4 (r & 3).  head_dim 64 (128-byte rows, two to a pass over the banks): K chunk c at
+// c ^ ((r >> 1) & 7), V chunk c at c ^ 4 ((r >> 1) & 1).  Both keep the 16-byte K reads and the
+// 8-byte transposed V reads of a wave free of bank conflicts.
+//
+// head_dim 64 has half the MFMA work per score, so the vector work of the softmax bounds it; its
+// registers and LDS let three workgroups share a CU.
+// Prefill of 4096 tokens, 32 heads over 8: 95.9 us with register staging (the general kernel) -> 81.7;
+// without the schedule groups 92, without the raised priority 92, two workgroups a CU 86 (profiled
+// kernel times, 85.5 as kept).
 #include "attn_common.h"
 #include "attn_dma.h"
 #include "launch.h"
@@ -29,13 +36,17 @@
 
 namespace nexus {
 
-template <bool CAP>
-__global__ __launch_bounds__(256, 2) void attn_bf16_d128_dma_kernel(const AttnArgs a,
-                                                                    const AttnPlan plan) {
-  constexpr int D = 128, KT = 64;
+template <int D, bool CAP>
+__global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
+    const AttnArgs a, const AttnPlan plan) {
+  static_assert(D == 64 || D == 128, "head_dim");
+  constexpr int KT = 64;
   constexpr int NKB = KT / 32, NDB = D / 32, NS = D / 16;
   constexpr int ROWB = D * 2;                 // bytes per K or V row
   constexpr int TILEB = KT * ROWB;            // bytes per K or V tile
+  constexpr int QTRB = TILEB / 4;             // a wave's quarter: one page
+  constexpr int CH = D / 8;                   // 16-byte chunks per row
+  constexpr int NI = QTRB / 1024;             // DMA instructions per quarter
   constexpr float kSlack = 8.0f;              // lazy rescale: p <= 2^8 between rescales
   constexpr int kPrioPV = 2;                  // wave priority of the PV phase
   __shared__ __align__(1024) char smem[2 * 2 * TILEB];   // K buffers 0, 1, V buffers 0, 1
@@ -90,20 +101,24 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_d128_dma_kernel(const AttnAr
   // ---- lane-invariant LDS read offsets
   uint32_t offk[NS];                          // S^T A operand: K row j, chunk 2s + hh
 #pragma unroll
-  for (int s = 0; s < NS; ++s) offk[s] = j * ROWB + (((2 * s + hh) ^ (j & 15)) * 16);
+  for (int s = 0; s < NS; ++s)
+    offk[s] = j * ROWB + (((2 * s + hh) ^ (D == 64 ? (j >> 1) & 7 : j & 15)) * 16);
   uint32_t offv[NDB];                         // PV A operand: see the header comment
   {
     const int gg = lane >> 4, r = lane & 15, e = r >> 2, q = r & 3;
     const int h2 = gg >> 1, dh = gg & 1;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
-      offv[db] = (4 * h2 + e) * ROWB + 32 * dh + 8 * q + 64 * (db ^ e);
+      offv[db] = (4 * h2 + e) * ROWB + 32 * dh + 8 * q + 64 * (db ^ (D == 64 ? e >> 1 : e));
   }
   // ---- DMA: wave w fills tile rows 16 w .. 16 w + 15 (one page).  Instruction i covers rows
-  // 4 i + r16; K chunk c of row r sits at c ^ (r & 15), V chunk c at c ^ 4 (r & 3).
-  const int r16 = lane >> 4;
-  const uint32_t kdo = r16 * ROWB + (((lane & 15) ^ r16) * 16);
-  const uint32_t vdo = r16 * ROWB + (((lane & 15) ^ (4 * r16)) * 16);
+  // i 64 / CH + lr, lane position lane % CH of the row; the source chunk undoes the swizzle (from
+  // one instruction to the next only bits of K's XOR change, V's repeats).
+  const int lr = lane / CH;
+  auto kswz = [](int row) { return D == 64 ? (row >> 1) & 7 : row & 15; };
+  auto vswz = [](int row) { return D == 64 ? 4 * ((row >> 1) & 1) : 4 * (row & 3); };
+  const uint32_t kdo = lr * ROWB + (((lane % CH) ^ kswz(lr)) * 16);
+  const uint32_t vdo = lr * ROWB + (((lane % CH) ^ vswz(lr)) * 16);
   const uint32_t smem_base = (uint32_t)(uintptr_t)smem;
   const uint64_t pbytes = (uint64_t)a.n_kv_heads * kPage * ROWB;   // one physical page
   const char *kbytes = reinterpret_cast<const char *>(a.kc) + (uint64_t)kvh * kPage * ROWB;
@@ -128,29 +143,33 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_d128_dma_kernel(const AttnAr
   auto dma_tile = [&](int it, int sel, char *dstp, uint32_t page) {
     const int kt = k_begin + it * KT;
     const char *src = sel ? vbytes : kbytes;
-    const uint32_t dst = smem_base + (uint32_t)(dstp - smem) + wave * 4096;
+    const uint32_t dst = smem_base + (uint32_t)(dstp - smem) + wave * QTRB;
     if (kt + KT <= k_end) {
       const char *ps = src + page * pbytes;
       if (sel) {
         dma_s<0>(dst, ps, vdo);
         dma_s<1024>(dst, ps, vdo);
-        dma_s<2048>(dst, ps, vdo);
-        dma_s<3072>(dst, ps, vdo);
+        if constexpr (D == 128) {
+          dma_s<2048>(dst, ps, vdo);
+          dma_s<3072>(dst, ps, vdo);
+        }
       } else {
         dma_s<0>(dst, ps, kdo);
-        dma_s<1024>(dst, ps, kdo ^ (1 << 6));
-        dma_s<2048>(dst, ps, kdo ^ (2 << 6));
-        dma_s<3072>(dst, ps, kdo ^ (3 << 6));
+        dma_s<1024>(dst, ps, kdo ^ (16u * kswz(64 / CH)));
+        if constexpr (D == 128) {
+          dma_s<2048>(dst, ps, kdo ^ (16u * kswz(2 * 64 / CH)));
+          dma_s<3072>(dst, ps, kdo ^ (16u * kswz(3 * 64 / CH)));
+        }
       }
     } else {
       const int tl = k_end - 1;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = 16 * wave + 4 * i + r16;
+      for (int i = 0; i < NI; ++i) {
+        const int row = 16 * wave + 64 / CH * i + lr;
         const int t = min(kt + row, tl);
         const uint64_t pp = (uint32_t)pg[(t >> kPageShift) - pg0];
         const uint32_t tok = (uint32_t)(t & (kPage - 1)) * ROWB;
-        const uint32_t c = sel ? ((lane & 15) ^ (4 * (row & 3))) : ((lane & 15) ^ (row & 15));
+        const uint32_t c = (lane % CH) ^ (sel ? vswz(row) : kswz(row));
         dma_v(dst + i * 1024, src + pp * pbytes + tok + c * 16);
       }
     }
@@ -301,12 +320,13 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_d128_dma_kernel(const AttnAr
       qk(kbuf(P ^ 1), s_nxt);
       softmax_block(s_cur[0], nm, pb);
       softmax_half(s_cur[1], 0, nm, pb[2]);
+      constexpr int VQ = D == 64 ? 10 : 5, VP = D == 64 ? 4 : 2, VM = D == 64 ? 12 : 6;
       __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
+      for (int i = 0; i < NKB * NS; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, VQ, 0);
       }
       // O += V P and what follows run at a raised wave priority: of the two waves that share a
       // SIMD, the one in this phase issues first
@@ -317,19 +337,19 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_d128_dma_kernel(const AttnAr
       softmax_half(s_cur[1], 1, nm, pb[3]);
       __builtin_amdgcn_sched_group_barrier(0x100, 4, 1);
 #pragma unroll
-      for (int i = 0; i < 12; ++i) {
+      for (int i = 0; i < 3 * NDB; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
-        __builtin_amdgcn_sched_group_barrier(0x002, 2, 1);
+        __builtin_amdgcn_sched_group_barrier(0x002, VP, 1);
       }
       pv_step(vl, 3, pb[3]);
       cap(s_nxt);
       mt_cur = row_max(s_nxt);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < NDB; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 2);
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 2);
-        __builtin_amdgcn_sched_group_barrier(0x002, 6, 2);
+        __builtin_amdgcn_sched_group_barrier(0x002, VM, 2);
       }
     }
     __builtin_amdgcn_s_setprio(0);
@@ -372,14 +392,16 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_d128_dma_kernel(const AttnAr
   }
 }
 
-hipError_t launch_attn_d128_dma(const AttnArgs &args, const AttnPlan &plan, int n_kv, bool cap,
-                                hipStream_t stream) {
+hipError_t launch_attn_dma(const AttnArgs &args, const AttnPlan &plan, int head_dim, int n_kv,
+                           bool cap, hipStream_t stream) {
   const dim3 grid(plan.units_per_head * n_kv);
-  if (cap)
-    hipLaunchKernelGGL(attn_bf16_d128_dma_kernel<true>, grid, dim3(256), 0, stream, args, plan);
-  else
-    hipLaunchKernelGGL(attn_bf16_d128_dma_kernel<false>, grid, dim3(256), 0, stream, args, plan);
-  return hipGetLastError();
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, args, plan);
+    return hipGetLastError();
+  };
+  if (head_dim == 64)
+    return cap ? run(attn_bf16_dma_kernel<64, true>) : run(attn_bf16_dma_kernel<64, false>);
+  return cap ? run(attn_bf16_dma_kernel<128, true>) : run(attn_bf16_dma_kernel<128, false>);
 }
 
 }  // namespace nexus

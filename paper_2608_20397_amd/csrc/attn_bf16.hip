@@ -11,7 +11,10 @@
 //   blockIdx.x % n_kv_heads selects the KV head, so on the 8-XCD MI355X every workgroup of one
 //   KV head lands on the same XCD and its K/V tiles are shared through that XCD's L2.
 //
-// Per 64-key tile and wave (head_dim 128)
+// The kernel here serves head_dim 256 with a row-major V (32-key tiles); head_dim 64 and 128 and the
+// transposed V of head_dim 256 have LDS-DMA kernels of their own, with the same plan and combine.
+//
+// Per key tile and wave
 //   S^T (keys x queries) = K . Q^T   with v_mfma_f32_32x32x16_bf16: A = K rows from LDS,
 //                                    B = Q held in registers for the whole kernel.
 //   Each lane then holds 32 scores of one query: the online softmax (log2 domain, fp32) needs
@@ -32,17 +35,17 @@
 
 namespace nexus {
 
-template <int D, int KT, bool VT, bool CAP>
-__global__ __launch_bounds__(256, (D >= 256 ? 1 : 2)) void attn_bf16_kernel(const AttnArgs a,
-                                                                             const AttnPlan plan) {
+template <bool CAP>
+__global__ __launch_bounds__(256, 1) void attn_bf16_d256_kernel(const AttnArgs a,
+                                                                const AttnPlan plan) {
+  constexpr int D = 256, KT = 32;
   constexpr int KCH = D / 8;                        // 16-byte chunks per K row
-  constexpr int KSW = (KCH < 16 ? KCH : 16) - 1;    // K row swizzle mask
+  constexpr int KSW = 15;                           // K row swizzle mask
   constexpr int VCH = KT / 8;                       // 16-byte chunks per V^T row
   constexpr int VSW = VCH - 1;
   constexpr int NKB = KT / 32;                      // 32-key score blocks per tile
   constexpr int NDB = D / 32;                       // 32-row blocks of O^T
   constexpr int NS = D / 16;                        // k-steps of Q K^T
-  constexpr int TPG = KT / kPage;                   // pages per tile
   constexpr float kSlack = 8.0f;                    // lazy rescale: p <= 2^8 between rescales
   __shared__ __align__(16) uint16_t Ks[2][KT * D];
   __shared__ __align__(16) uint16_t Vs[2][D * KT];
@@ -103,24 +106,16 @@ __global__ __launch_bounds__(256, (D >= 256 ? 1 : 2)) void attn_bf16_kernel(cons
   const uint32_t pstride = (uint32_t)a.n_kv_heads * kPage * D;   // one physical page, all heads
   const uint16_t *kbase = a.kc + (int64_t)kvh * kPage * D;
   const uint16_t *vbase = a.vc + (int64_t)kvh * kPage * D;
-  const uint32_t n_cols = (uint32_t)a.n_phys_pages * kPage;        // transposed V row length
-  const uint16_t *vtbase = a.vc + (int64_t)kvh * D * n_cols;
 
   // ---- per-thread staging assignment (invariant over tiles)
   constexpr int K_ITEMS = KT * KCH / 256;                   // 16-byte K chunks per thread
-  constexpr int V_ITEMS_RM = (KT / 4) * (D / 8);            // (4-token, 8-dim) groups
-  constexpr int V_PER_T_RM = (V_ITEMS_RM + 255) / 256;
-  constexpr int V_ITEMS_T = D * (KT / 8);                   // (dim, 8-token) groups
-  constexpr int V_PER_T_T = V_ITEMS_T / 256;
-  static_assert(K_ITEMS >= 1 && KT * KCH % 256 == 0, "tile too small");
-  static_assert(V_PER_T_RM == 1 || VT, "one V group per thread");
-  // staging registers of the tiles on their way to LDS: with head_dim 256 (one workgroup per
-  // CU, registers to spare) two tiles are in flight, else one
-  constexpr int NPRE = D >= 256 ? 2 : 1;
-  constexpr int VN = VT ? V_PER_T_T : 4;
+  static_assert(KT * KCH % 256 == 0 && (KT / 4) * (D / 8) == 256, "one V group per thread");
+  // staging registers of the tiles on their way to LDS: two tiles are in flight (one workgroup per
+  // CU, registers to spare)
+  constexpr int NPRE = 2;
   struct Stage {
     u32x4 k[K_ITEMS];
-    u32x4 v[VN];
+    u32x4 v[4];
   };
   Stage stg[NPRE];
 
@@ -128,8 +123,6 @@ __global__ __launch_bounds__(256, (D >= 256 ? 1 : 2)) void attn_bf16_kernel(cons
   const int kc = tid % KCH;
   // V row-major: 4 tokens (4 vg4 .. 4 vg4 + 3) x 8 dims (8 vdc ..)
   const int vg4 = tid / (D / 8), vdc = tid % (D / 8);
-  constexpr bool kAllOwnV = VT || V_ITEMS_RM >= 256;
-  const bool v_owner = kAllOwnV || tid < V_ITEMS_RM;
 
   __syncthreads();   // pg[] visible
 
@@ -137,7 +130,7 @@ __global__ __launch_bounds__(256, (D >= 256 ? 1 : 2)) void attn_bf16_kernel(cons
   // their K/V are finite; their scores are masked and their weights are exactly 0.  Global
   // addresses are a uniform base plus a 32-bit unsigned byte offset.
   const char *kbytes = reinterpret_cast<const char *>(kbase);
-  const char *vbytes = reinterpret_cast<const char *>(VT ? vtbase : vbase);
+  const char *vbytes = reinterpret_cast<const char *>(vbase);
   auto load_tile = [&](int it, Stage &sg) {
     const int kt = k_begin + it * KT;
     const int tl = k_end - 1;
@@ -149,36 +142,13 @@ __global__ __launch_bounds__(256, (D >= 256 ? 1 : 2)) void attn_bf16_kernel(cons
       const uint32_t off = (__umul24(page, pstride) + (t & (kPage - 1)) * D + kc * 8) * 2u;
       sg.k[i] = *reinterpret_cast<const u32x4 *>(kbytes + off);
     }
-    if constexpr (!VT) {
-      if (kAllOwnV || v_owner) {
-        const uint32_t t0 = (uint32_t)min(kt + 4 * vg4, tl);
-        const uint32_t page = (uint32_t)pg[(t0 >> kPageShift) - pg0];
-        const uint32_t base = __umul24(page, pstride) + vdc * 8;
+    const uint32_t t0 = (uint32_t)min(kt + 4 * vg4, tl);
+    const uint32_t page = (uint32_t)pg[(t0 >> kPageShift) - pg0];
+    const uint32_t base = __umul24(page, pstride) + vdc * 8;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t t = (uint32_t)min(kt + 4 * vg4 + e, tl);
-          sg.v[e] = *reinterpret_cast<const u32x4 *>(vbytes + (base + (t & (kPage - 1)) * D) * 2u);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < V_PER_T_T; ++i) {
-        const int u = tid + 256 * i;
-        const int d = u / (KT / 8), grp = u % (KT / 8);
-        const int t0 = min(kt + 8 * grp, tl & ~7);   // 8-token group holding key t0
-        const uint32_t page = (uint32_t)pg[(t0 >> kPageShift) - pg0];
-        u32x4 val = *reinterpret_cast<const u32x4 *>(
-            vbytes + ((uint32_t)d * n_cols + page * kPage + (uint32_t)(t0 & (kPage - 1))) * 2u);
-        if (kt + 8 * grp + 8 > k_end) {
-          // group crosses or lies past the split end: keep keys <= tl, zero the rest (slots
-          // past the end of the written cache may hold anything)
-          const int nvalid = max(0, min(8, k_end - (kt + 8 * grp)));
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (e >= nvalid) val[e >> 1] &= (e & 1) ? 0x0000FFFFu : 0xFFFF0000u;
-        }
-        sg.v[i] = val;
-      }
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t t = (uint32_t)min(kt + 4 * vg4 + e, tl);
+      sg.v[e] = *reinterpret_cast<const u32x4 *>(vbytes + (base + (t & (kPage - 1)) * D) * 2u);
     }
   };
 
@@ -190,36 +160,18 @@ __global__ __launch_bounds__(256, (D >= 256 ? 1 : 2)) void attn_bf16_kernel(cons
       const int key = (tid + 256 * i) / KCH;
       *reinterpret_cast<u32x4 *>(ks + key * D + ((kc ^ (key & KSW)) * 8)) = sg.k[i];
     }
-    if constexpr (!VT) {
-      if (kAllOwnV || v_owner) {
-        const int pos = (4 * vg4 & ~15) | vt_pos(4 * vg4 & 15);   // 4-aligned
-        const int cc = pos >> 3, half = (pos >> 2) & 1;
+    const int pos = (4 * vg4 & ~15) | vt_pos(4 * vg4 & 15);   // 4-aligned
+    const int cc = pos >> 3, half = (pos >> 2) & 1;
 #pragma unroll
-        for (int dd = 0; dd < 8; ++dd) {
-          const int wi = dd >> 1;
-          // gather feature dd of the 4 tokens: low or high halves of word wi
-          const uint32_t sel = (dd & 1) ? 0x07060302u : 0x05040100u;
-          const uint32_t lo = __builtin_amdgcn_perm(sg.v[1][wi], sg.v[0][wi], sel);
-          const uint32_t hi = __builtin_amdgcn_perm(sg.v[3][wi], sg.v[2][wi], sel);
-          const int d = 8 * vdc + dd;
-          *reinterpret_cast<u32x2 *>(vs + d * KT + ((cc ^ vt_swz<VSW>(d)) * 8) + half * 4) =
-              u32x2{lo, hi};
-        }
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < V_PER_T_T; ++i) {
-        const int u = tid + 256 * i;
-        const int d = u / (KT / 8), grp = u % (KT / 8);
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-          const int k4 = 8 * grp + 4 * hf;
-          const int pos = (k4 & ~15) | vt_pos(k4 & 15);
-          const int cc = pos >> 3, half = (pos >> 2) & 1;
-          const u32x2 piece = hf ? u32x2{sg.v[i][2], sg.v[i][3]} : u32x2{sg.v[i][0], sg.v[i][1]};
-          *reinterpret_cast<u32x2 *>(vs + d * KT + ((cc ^ vt_swz<VSW>(d)) * 8) + half * 4) = piece;
-        }
-      }
+    for (int dd = 0; dd < 8; ++dd) {
+      const int wi = dd >> 1;
+      // gather feature dd of the 4 tokens: low or high halves of word wi
+      const uint32_t sel = (dd & 1) ? 0x07060302u : 0x05040100u;
+      const uint32_t lo = __builtin_amdgcn_perm(sg.v[1][wi], sg.v[0][wi], sel);
+      const uint32_t hi = __builtin_amdgcn_perm(sg.v[3][wi], sg.v[2][wi], sel);
+      const int d = 8 * vdc + dd;
+      *reinterpret_cast<u32x2 *>(vs + d * KT + ((cc ^ vt_swz<VSW>(d)) * 8) + half * 4) =
+          u32x2{lo, hi};
     }
   };
 
@@ -324,13 +276,9 @@ __global__ __launch_bounds__(256, (D >= 256 ? 1 : 2)) void attn_bf16_kernel(cons
     if (it + 1 + NPRE < n_tiles) load_tile(it + 1 + NPRE, nxt);
     __syncthreads();
   };
-  if constexpr (NPRE == 1) {
-    for (int it = 0; it < n_tiles; ++it) step(it, stg[0]);
-  } else {
-    for (int it = 0; it < n_tiles; it += 2) {
-      step(it, stg[1]);
-      if (it + 1 < n_tiles) step(it + 1, stg[NPRE - 2]);
-    }
+  for (int it = 0; it < n_tiles; it += 2) {
+    step(it, stg[1]);
+    if (it + 1 < n_tiles) step(it + 1, stg[0]);
   }
 
   // ---- epilogue
@@ -444,8 +392,6 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const AttnArgs a, con
 
 namespace {
 
-int key_tile_for(int head_dim) { return head_dim >= 256 ? 32 : 64; }
-
 // Geometry of the kernel that serves a launch: queries per wave task, key tile, how many of its
 // workgroups are resident per CU, wave tasks per workgroup, and the plan's time per key of one
 // workgroup (us, measured).
@@ -455,11 +401,10 @@ struct KernelShape {
 };
 
 KernelShape kernel_shape(const AttnLaunch &p) {
-  if (p.head_dim == 128 && !p.v_transposed) return {kQB, 64, 2, kWaves, 0.03};   // LDS DMA
-  if (p.head_dim == 64 && !p.v_transposed) return {kQB, 64, 3, kWaves, 0.015};   // LDS DMA
-  if (p.head_dim == 256 && p.v_transposed) return {kQB, 32, 1, kWavesWide, 0.04};   // LDS DMA
-  return {kQB, key_tile_for(p.head_dim), p.head_dim >= 256 ? 1 : 2, kWaves,
-          0.03 * p.head_dim / 128.0};
+  if (p.head_dim == 128) return {kQB, 64, 2, kWaves, 0.03};   // LDS DMA
+  if (p.head_dim == 64) return {kQB, 64, 3, kWaves, 0.015};   // LDS DMA
+  if (p.v_transposed) return {kQB, 32, 1, kWavesWide, 0.04};   // LDS DMA
+  return {kQB, 32, 1, kWaves, 0.06};
 }
 
 constexpr int kCUs = 256;
@@ -739,22 +684,11 @@ bool make_plan(const AttnLaunch &p, AttnPlan &plan) {
   return true;
 }
 
-template <int D, int KT, bool VT>
-hipError_t launch_main(const AttnArgs &args, const AttnPlan &plan, int n_kv, bool cap,
-                       hipStream_t stream) {
-  const dim3 grid(plan.units_per_head * n_kv);
-  if (cap)
-    hipLaunchKernelGGL((attn_bf16_kernel<D, KT, VT, true>), grid, dim3(256), 0, stream, args, plan);
-  else
-    hipLaunchKernelGGL((attn_bf16_kernel<D, KT, VT, false>), grid, dim3(256), 0, stream, args, plan);
-  return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t launch_attention_f32(const AttnLaunch &p, hipStream_t stream);
-hipError_t launch_attn_dma(const AttnArgs &args, const AttnPlan &plan, int head_dim, int n_kv,
-                           bool cap, hipStream_t stream);
+hipError_t launch_attn_d128_dma(const AttnArgs &args, const AttnPlan &plan, int n_kv, bool cap,
+                                hipStream_t stream);   // head_dim up to 128
 hipError_t launch_attn_d256_vt(const AttnArgs &args, const AttnPlan &plan, int n_kv, bool cap,
                                hipStream_t stream);
 
@@ -782,6 +716,8 @@ hipError_t launch_attention(const AttnLaunch &p, hipStream_t stream) {
   args.n_kv_heads = p.n_kv_heads;
   args.group = p.n_q_heads / p.n_kv_heads;
   args.n_phys_pages = p.n_phys_pages;
+  args.head_dim = p.head_dim;
+  args.v_transposed = p.v_transposed;
   const float log2e = 1.4426950408889634f;
   args.scale_log2 = p.scale * log2e;
   args.cap_in = p.softcap > 0.f ? p.scale / p.softcap : 0.f;
@@ -790,16 +726,19 @@ hipError_t launch_attention(const AttnLaunch &p, hipStream_t stream) {
   const bool cap = p.softcap > 0.f;
   const bool vt = p.v_transposed;
   hipError_t e = hipSuccess;
-  if (p.head_dim <= 128 && !vt)
-    e = launch_attn_dma(args, plan, p.head_dim, p.n_kv_heads, cap, stream);
-  else if (p.head_dim == 64)
-    e = launch_main<64, 64, true>(args, plan, p.n_kv_heads, cap, stream);
-  else if (p.head_dim == 128)
-    e = launch_main<128, 64, true>(args, plan, p.n_kv_heads, cap, stream);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(plan.units_per_head * p.n_kv_heads), dim3(256), 0, stream, args,
+                       plan);
+    return hipGetLastError();
+  };
+  if (p.head_dim <= 128)
+    e = launch_attn_d128_dma(args, plan, p.n_kv_heads, cap, stream);
   else if (vt)
     e = launch_attn_d256_vt(args, plan, p.n_kv_heads, cap, stream);
+  else if (cap)
+    e = run(attn_bf16_d256_kernel<true>);
   else
-    e = launch_main<256, 32, false>(args, plan, p.n_kv_heads, cap, stream);
+    e = run(attn_bf16_d256_kernel<false>);
   if (e != hipSuccess) return e;
   if (plan.any_split) {
     const int64_t total = (int64_t)plan.total_rows * p.n_q_heads * (p.head_dim / 16);

@@ -1,7 +1,7 @@
-// bf16 suffix attention, head_dim 64 and 128 with a row-major V cache: the variant that feeds LDS
-// with gfx950's LDS DMA loads (Sec. III-A; the re-decoded suffix of Sec. VI-A).
+// bf16 suffix attention, head_dim 64 and 128: the kernel that feeds LDS with gfx950's LDS DMA loads
+// (Sec. III-A; the re-decoded suffix of Sec. VI-A; transposed V per Sec. VI-B).
 //
-// Same work decomposition and math as attn_bf16_kernel (one KV head per workgroup, 4 waves, each
+// Same work decomposition and math as attn_bf16_d256_kernel (one KV head per workgroup, 4 waves, each
 // wave one query head x 32 queries, S^T = K.Q^T and O^T += V^T.P^T on 32x32x16 MFMA, online
 // softmax in log2 units with a lazily moved reference, two workgroups per CU so that one
 // workgroup's softmax overlaps the other's MFMA work), but:
@@ -17,17 +17,23 @@
 //     8 bytes that source lane 4e + i / 4 points at, e = 0..3.  Source lane 4e + q points at
 //     V[key_e][d0 + 4q], so output lane i receives V[key_0..3][d0 + i].  The keys each lane
 //     needs follow the score layout of the S^T MFMA (keys 4h..4h+3 and 8+4h..8+4h+3 of a
-//     16-key step for lane half h).
+//     16-key step for lane half h);
+//   * a transposed V tile (64 keys of every feature, 128-byte rows) is loaded 8 keys a lane through the
+//     page of those keys, and read back 8 keys at a time: with transposed V the K rows enter S^T
+//     in the order that leaves a lane 8 consecutive keys of each 16-key step.
 // LDS tiles, head_dim 128: K row r (256 B) holds chunk c at c ^ (r & 15); V row r holds chunk c at
 // c ^ 4 (r & 3).  head_dim 64 (128-byte rows, two to a pass over the banks): K chunk c at
 // c ^ ((r >> 1) & 7), V chunk c at c ^ 4 ((r >> 1) & 1).  Both keep the 16-byte K reads and the
-// 8-byte transposed V reads of a wave free of bank conflicts.
+// 8-byte transposed V reads of a wave free of bank conflicts; so does a transposed V tile's chunk c of
+// feature row d at c ^ ((d >> 1) & 7).
 //
 // head_dim 64 has half the MFMA work per score, so the vector work of the softmax bounds it; its
 // registers and LDS let three workgroups share a CU.
 // Prefill of 4096 tokens, 32 heads over 8: 95.9 us with register staging (the general kernel) -> 81.7;
 // without the schedule groups 92, without the raised priority 92, two workgroups a CU 86 (profiled
 // kernel times, 85.5 as kept).
+// Transposed V, head_dim 128, against register staging (profiled kernel times): 1088 queries over 9280
+// keys 320 -> 252 us, a prefill of 2048 78 -> 68, 192 queries over 2624 keys 28.6 -> 25.2.
 #include "attn_common.h"
 #include "attn_dma.h"
 #include "launch.h"
@@ -36,7 +42,7 @@
 
 namespace nexus {
 
-template <int D, bool CAP>
+template <int D, bool VT, bool CAP>
 __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
     const AttnArgs a, const AttnPlan plan) {
   static_assert(D == 64 || D == 128, "head_dim");
@@ -47,6 +53,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
   constexpr int QTRB = TILEB / 4;             // a wave's quarter: one page
   constexpr int CH = D / 8;                   // 16-byte chunks per row
   constexpr int NI = QTRB / 1024;             // DMA instructions per quarter
+  constexpr int VROWB = KT * 2;               // bytes per feature row of a transposed V tile
   constexpr float kSlack = 8.0f;              // lazy rescale: p <= 2^8 between rescales
   constexpr int kPrioPV = 2;                  // wave priority of the PV phase
   __shared__ __align__(1024) char smem[2 * 2 * TILEB];   // K buffers 0, 1, V buffers 0, 1
@@ -98,13 +105,18 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
   float m_ref = -INFINITY;
   float l = 0.f;
 
-  // ---- lane-invariant LDS read offsets
+  // ---- lane-invariant LDS read offsets; score row j belongs to key kj of its 32 (transposed V: bits
+  // 2 and 3 swapped, so that a lane's scores of 16 keys are 8 consecutive ones)
+  const int kj = VT ? vt_pos(j) : j;
   uint32_t offk[NS];                          // S^T A operand: K row j, chunk 2s + hh
 #pragma unroll
   for (int s = 0; s < NS; ++s)
-    offk[s] = j * ROWB + (((2 * s + hh) ^ (D == 64 ? (j >> 1) & 7 : j & 15)) * 16);
+    offk[s] = kj * ROWB + (((2 * s + hh) ^ (D == 64 ? (kj >> 1) & 7 : kj & 15)) * 16);
   uint32_t offv[NDB];                         // PV A operand: see the header comment
-  {
+  if constexpr (VT) {
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) offv[db] = (32 * db + j) * VROWB;   // chunk added in pv_step
+  } else {
     const int gg = lane >> 4, r = lane & 15, e = r >> 2, q = r & 3;
     const int h2 = gg >> 1, dh = gg & 1;
 #pragma unroll
@@ -122,7 +134,18 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
   const uint32_t smem_base = (uint32_t)(uintptr_t)smem;
   const uint64_t pbytes = (uint64_t)a.n_kv_heads * kPage * ROWB;   // one physical page
   const char *kbytes = reinterpret_cast<const char *>(a.kc) + (uint64_t)kvh * kPage * ROWB;
-  const char *vbytes = reinterpret_cast<const char *>(a.vc) + (uint64_t)kvh * kPage * ROWB;
+  const uint32_t n_cols = (uint32_t)a.n_phys_pages * kPage;        // transposed V row length
+  const char *vbytes = reinterpret_cast<const char *>(a.vc) +
+                       (VT ? (uint64_t)kvh * D * n_cols * 2 : (uint64_t)kvh * kPage * ROWB);
+  // transposed V: wave w fills feature rows w D / 4 .. of the tile, 8 rows an instruction, lane position
+  // lane % 8; in instruction i that is key chunk vc ^ 4 (i & 1), of the tile's page vp ^ 2 (i & 1)
+  const int vc = (lane & 7) ^ (lane >> 4), vp = vc >> 1;
+  const uint32_t vto = ((uint32_t)(wave * (D / 4) + (lane >> 3)) * n_cols + 8 * (vc & 1)) * 2;
+  uint32_t vpg[2];                                                 // pages of the next V tile's DMA
+  auto v_pages = [&](int it) {
+    vpg[0] = (uint32_t)pg[min(it * (KT / kPage) + vp, n_pg - 1)];
+    vpg[1] = (uint32_t)pg[min(it * (KT / kPage) + (vp ^ 2), n_pg - 1)];
+  };
   auto kbuf = [&](int i) { return smem + i * TILEB; };
   auto vbuf = [&](int i) { return smem + (2 + i) * TILEB; };
 
@@ -144,7 +167,11 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
     const int kt = k_begin + it * KT;
     const char *src = sel ? vbytes : kbytes;
     const uint32_t dst = smem_base + (uint32_t)(dstp - smem) + wave * QTRB;
-    if (kt + KT <= k_end) {
+    if (VT && sel) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        dma_s<0>(dst + i * 1024, src, vto + vpg[i & 1] * (2 * kPage) + (uint32_t)i * 16 * n_cols);
+    } else if (kt + KT <= k_end) {
       const char *ps = src + page * pbytes;
       if (sel) {
         dma_s<0>(dst, ps, vdo);
@@ -172,6 +199,24 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
         const uint32_t c = (lane % CH) ^ (sel ? vswz(row) : kswz(row));
         dma_v(dst + i * 1024, src + pp * pbytes + tok + c * 16);
       }
+    }
+  };
+  // slots past the sequence end may hold anything: once a partial transposed V tile has landed, the wave
+  // clears their keys in its quarter
+  auto clear_tail = [&](int it, char *dstp) {
+    const int nvalid = k_end - (k_begin + it * KT);
+    if (!VT || nvalid >= KT) return;
+    asm volatile("" ::: "memory");            // the tile is read after the wait for it
+    for (int x = lane; x < (D / 4) * 8; x += 64) {
+      const int row = wave * (D / 4) + (x >> 3), c = x & 7;
+      const int keep = nvalid - 8 * c;
+      if (keep >= 8) continue;
+      u32x4 *at = reinterpret_cast<u32x4 *>(dstp + row * VROWB + 16 * (c ^ ((row >> 1) & 7)));
+      u32x4 val = *at;
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+        val[w] = 2 * w + 1 < keep ? val[w] : 2 * w < keep ? val[w] & 0xFFFFu : 0u;
+      *at = val;
     }
   };
   auto full = [&](int it) { return k_begin + it * KT + KT <= k_end; };
@@ -210,12 +255,13 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
   };
   // causal / tail mask of S(t) (tiles for which needs_mask(t))
   auto mask = [&](f32x16 *sc, int t) {
-    const int lim = min(qpos0 + j, k_end - 1) - (k_begin + t * KT) - 4 * hh;
+    const int lim = min(qpos0 + j, k_end - 1) - (k_begin + t * KT) - (VT ? 8 : 4) * hh;
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
       for (int v = 0; v < 16; ++v)
-        if (32 * kb + 8 * (v >> 2) + (v & 3) > lim) sc[kb][v] = -INFINITY;
+        if (32 * kb + (VT ? 16 * (v >> 3) + (v & 7) : 8 * (v >> 2) + (v & 3)) > lim)
+          sc[kb][v] = -INFINITY;
   };
   // row maximum of S(t) in log2 units
   auto row_max = [&](const f32x16 *sc) -> float {
@@ -257,8 +303,14 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
   auto pv_step = [&](const char *vl, int ks, const bf16x8 &pbv) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db) {
-      const char *p = vl + ks * 16 * ROWB + offv[db];
-      const bf16x8 va = tr_read_pair(p, p + 8 * ROWB);
+      bf16x8 va;
+      if constexpr (VT) {
+        va = *reinterpret_cast<const bf16x8 *>(vl + offv[db] +
+                                               16 * ((2 * ks + hh) ^ ((j >> 1) & 7)));
+      } else {
+        const char *p = vl + ks * 16 * ROWB + offv[db];
+        va = tr_read_pair(p, p + 8 * ROWB);
+      }
       o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pbv, o[db], 0, 0, 0);
     }
   };
@@ -275,8 +327,10 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
   uint32_t pgv = 0, pk = 0;
   if (n_tiles > 0) {
     const uint32_t p0 = full(0) ? page_of(0) : 0;
+    if constexpr (VT) v_pages(0);
     dma_tile(0, 0, kbuf(0), p0);
     dma_tile(0, 1, vbuf(0), p0);
+    if constexpr (VT) v_pages(1);
     if (n_tiles > 1) {
       pgv = full(1) ? page_of(1) : 0;
       dma_tile(1, 0, kbuf(1), pgv);
@@ -284,6 +338,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
     if (n_tiles > 2 && full(2)) pk = page_of(2);
   }
   wait_vm<0>();
+  if (n_tiles > 0) clear_tail(0, vbuf(0));
   tile_barrier();
   float mt_cur = -INFINITY;                     // row maximum of S(t), log2 units
   if (active && n_tiles > 0) {
@@ -335,11 +390,11 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
       pv_step(vl, 1, pb[1]);
       pv_step(vl, 2, pb[2]);
       softmax_half(s_cur[1], 1, nm, pb[3]);
-      __builtin_amdgcn_sched_group_barrier(0x100, 4, 1);
+      __builtin_amdgcn_sched_group_barrier(0x100, VT ? 2 : 4, 1);
 #pragma unroll
       for (int i = 0; i < 3 * NDB; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
+        __builtin_amdgcn_sched_group_barrier(0x100, VT ? 1 : 2, 1);
         __builtin_amdgcn_sched_group_barrier(0x002, VP, 1);
       }
       pv_step(vl, 3, pb[3]);
@@ -348,7 +403,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
 #pragma unroll
       for (int i = 0; i < NDB; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 2);
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 2);
+        __builtin_amdgcn_sched_group_barrier(0x100, VT ? 1 : 2, 2);
         __builtin_amdgcn_sched_group_barrier(0x002, VM, 2);
       }
     }
@@ -356,8 +411,10 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
     // pages for the next iteration's DMA (the LDS read overlaps the wait below)
     pgv = pk;
     if (t + 3 < n_tiles && full(t + 3)) pk = page_of(t + 3);
+    if constexpr (VT) v_pages(t + 2);
     // K[t + 2] and V[t + 1], issued above, are read in the next iteration
     wait_vm<0>();
+    if (t + 1 < n_tiles) clear_tail(t + 1, vbuf(P ^ 1));
     tile_barrier();
   };
   // Every iteration computes S(t + 1): on the last tile from a K buffer whose contents are
@@ -392,16 +449,22 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
   }
 }
 
-hipError_t launch_attn_dma(const AttnArgs &args, const AttnPlan &plan, int head_dim, int n_kv,
-                           bool cap, hipStream_t stream) {
+hipError_t launch_attn_d128_dma(const AttnArgs &args, const AttnPlan &plan, int n_kv, bool cap,
+                                hipStream_t stream) {
   const dim3 grid(plan.units_per_head * n_kv);
   auto run = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, args, plan);
     return hipGetLastError();
   };
-  if (head_dim == 64)
-    return cap ? run(attn_bf16_dma_kernel<64, true>) : run(attn_bf16_dma_kernel<64, false>);
-  return cap ? run(attn_bf16_dma_kernel<128, true>) : run(attn_bf16_dma_kernel<128, false>);
+  auto with_cap = [&](auto d, auto v) {
+    return cap ? run(attn_bf16_dma_kernel<d(), v(), true>)
+               : run(attn_bf16_dma_kernel<d(), v(), false>);
+  };
+  auto with_v = [&](auto d) {
+    return args.v_transposed ? with_cap(d, std::true_type{}) : with_cap(d, std::false_type{});
+  };
+  return args.head_dim == 64 ? with_v(std::integral_constant<int, 64>{})
+                        : with_v(std::integral_constant<int, 128>{});
 }
 
 }  // namespace nexus

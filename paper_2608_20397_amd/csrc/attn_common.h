@@ -140,6 +140,7 @@ struct AttnArgs {
   const int32_t *map;
   char *ws;             // split partials: fp16 rows at SeqPlan::ws_off, records at ml_off
   int32_t n_q_heads, n_kv_heads, group, n_phys_pages;
+  int32_t head_dim, v_transposed;   // of the launch (the kernels know their own)
   float scale_log2;     // scale * log2(e)
   float cap_in;         // scale / softcap
   float cap_out;        // softcap * log2(e)

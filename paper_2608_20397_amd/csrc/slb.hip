@@ -317,7 +317,9 @@ __global__ __launch_bounds__(256) void slb_scan_kernel(SlbArgs a) {
 // The best score of each tile (its ordered pattern; 0 for a tile past the registry) goes to
 // part[query][tile].  Keeping a sorted list per lane here instead, a wave inserts nearly every
 // score it meets, because it meets few tools: 65536 tools x 256 queries of dim 768, k 8, whole
-// call: 125 us, this way 47.5 (this pass 34, the second 14).
+// call: 125 us, this way 46.7 (this pass 33, the second 14).
+// Its time grows with dim x queries at about a fifth of the int8 MFMA rate; two more chunks in flight, 8
+// waves a workgroup and an unbranched loop changed nothing (34.5, 35.8, 33.8).
 __device__ __forceinline__ uint32_t score_order(float score) {
   const uint32_t u = __float_as_uint(score);
   return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
@@ -427,13 +429,18 @@ __global__ __launch_bounds__(256, 2) void slb_max_kernel(SlbArgs a) {
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
       const f32x4 sc = *reinterpret_cast<const f32x4 *>(tsc + tb + 16 * i + 4 * grp);
-      const int left = t_end - (t_begin + tb + 16 * i + 4 * grp);   // tools the registry still has
+      // all ones for a tool of the registry, 0 past its end: an AND, where a selection became a branch
+      // around every score (4096 tools x 32 queries of 384: 9.6 against 7.7 us)
+      uint32_t in[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        in[r] = (uint32_t)((t_begin + tb + 16 * i + 4 * grp + r - t_end) >> 31);
 #pragma unroll
       for (int sb = 0; sb < NSB; ++sb) {
         uint32_t x[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          x[r] = r < left ? score_order(((float)acc[i][sb][r] * sc[r]) * sq[sb]) : 0u;
+          x[r] = score_order(((float)acc[i][sb][r] * sc[r]) * sq[sb]) & in[r];
         m[i][sb] = umax(umax(x[0], x[1]), umax(x[2], x[3]));
       }
     }

@@ -909,7 +909,7 @@ def main():
         },
         "roofline": {
             "bound": "mfma",
-            "kernel": ("one nexus_suffix_attn call per layer: attn_bf16_d128_dma_kernel + "
+            "kernel": ("one nexus_suffix_attn call per layer: attn_bf16_dma_kernel + "
                        "attn_combine_kernel (split-K combine)"),
             "achieved": attn_tflops,
             "peak": MFMA_BF16_PEAK_TFLOPS,

@@ -119,12 +119,15 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise NexusError(EDTYPE, f"unsupported dtype {t.dtype}")
 
 
+# Both return plain integers, which ctypes passes for a void pointer: an object for each of a call's ten
+# pointers and a Stream object for its stream took 6 of the 29 us that quantising one query and scanning
+# 250 tools cost the host.
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p(0)
+    return t.data_ptr() if t is not None else 0
 
 
 def _on_device(*named):

@@ -42,7 +42,7 @@
 
 namespace nexus {
 
-template <int D, bool VT, bool CAP>
+template <int D, bool VT, bool CAP, bool DMA>
 __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
     const AttnArgs a, const AttnPlan plan) {
   static_assert(D == 64 || D == 128, "head_dim");
@@ -167,6 +167,28 @@ __global__ __launch_bounds__(256, (D == 64 ? 3 : 2)) void attn_bf16_dma_kernel(
     const int kt = k_begin + it * KT;
     const char *src = sel ? vbytes : kbytes;
     const uint32_t dst = smem_base + (uint32_t)(dstp - smem) + wave * QTRB;
+    if constexpr (!DMA) {
+      // caches whose base is not 16-byte aligned: the same 16 bytes a lane through registers
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const char *from;
+        if (VT && sel) {
+          from = src + (uint32_t)(vto + vpg[i & 1] * (2 * kPage) + (uint32_t)i * 16 * n_cols);
+        } else if (kt + KT <= k_end) {
+          from = src + page * pbytes + 1024 * i + (sel ? vdo : kdo ^ (16u * kswz(i * 64 / CH)));
+        } else {
+          const int row = 16 * wave + 64 / CH * i + lr;
+          const int t = min(kt + row, k_end - 1);
+          const uint64_t pp = (uint32_t)pg[(t >> kPageShift) - pg0];
+          const uint32_t c = (lane % CH) ^ (sel ? vswz(row) : kswz(row));
+          from = src + pp * pbytes + (uint32_t)(t & (kPage - 1)) * ROWB + c * 16;
+        }
+        u32x4 val;
+        __builtin_memcpy(&val, __builtin_assume_aligned(from, 2), 16);
+        *reinterpret_cast<u32x4 *>(dstp + wave * QTRB + i * 1024 + 16 * lane) = val;
+      }
+      return;
+    }
     if (VT && sel) {
 #pragma unroll
       for (int i = 0; i < NI; ++i)
@@ -457,8 +479,11 @@ hipError_t launch_attn_d128_dma(const AttnArgs &args, const AttnPlan &plan, int 
     return hipGetLastError();
   };
   auto with_cap = [&](auto d, auto v) {
-    return cap ? run(attn_bf16_dma_kernel<d(), v(), true>)
-               : run(attn_bf16_dma_kernel<d(), v(), false>);
+    if ((uintptr_t)args.kc % 16 != 0 || (uintptr_t)args.vc % 16 != 0)
+      return cap ? run(attn_bf16_dma_kernel<d(), v(), true, false>)
+                 : run(attn_bf16_dma_kernel<d(), v(), false, false>);
+    return cap ? run(attn_bf16_dma_kernel<d(), v(), true, true>)
+               : run(attn_bf16_dma_kernel<d(), v(), false, true>);
   };
   auto with_v = [&](auto d) {
     return args.v_transposed ? with_cap(d, std::true_type{}) : with_cap(d, std::false_type{});

@@ -1041,7 +1041,10 @@ size_t decode_workspace_bytes(const DecodeLaunch &p) {
 hipError_t launch_decode(const DecodeLaunch &p, hipStream_t stream) {
   const int group = p.n_q_heads / p.n_kv_heads;
   const int n_qgroups = (group + 15) / 16;
-  const DecodeShape sh = decode_shape(p);
+  DecodeShape sh = decode_shape(p);
+  // shared pages travel by LDS DMA, 16 aligned bytes a lane: a cache that starts elsewhere is read
+  // sequence by sequence
+  if ((uintptr_t)p.cache_k % 16 != 0 || (uintptr_t)p.cache_v % 16 != 0) sh.n_groups = 0;
   const int slots = sh.slots();
   DecodeArgs a{};
   const size_t esize = p.is_bf16 ? 2 : 4;

@@ -57,3 +57,27 @@ def test_pieces(d, vt, cap, n_s, n_past):
     ma, rr = compare(got, ref)
     print(f"max-abs {ma:.3e} rel-RMS {rr:.3e}", flush=True)
     assert ma <= BF16_MAX_ABS and rr <= BF16_REL_RMS, (ma, rr)
+
+
+@pytest.mark.parametrize("d,vt", [(64, False), (64, True), (128, False), (128, True)])
+def test_cache_base_not_16_byte_aligned(d, vt):
+    """The same bits from a cache that starts 2 bytes past a 16-byte boundary."""
+    n_kv, g, n_s, n_past = 2, 2, 75, 700
+    npp = (n_s + n_past + PAGE - 1) // PAGE
+    shape = (1, npp, n_kv, PAGE, d)
+    k = G.device_normal(2, 1, 1, shape, 1.0, "bf16", "cuda")
+    v = G.device_normal(2, 1, 2, (1, n_kv, d, npp * PAGE) if vt else shape, 0.1, "bf16", "cuda")
+    q = G.device_normal(2, 1, 0, (n_s, n_kv * g, d), 0.1, "bf16", "cuda")
+    pm = torch.from_numpy(np.random.default_rng(3).permutation(npp).astype(np.int32)).cuda()
+    outs = []
+    for shift in (0, 1):
+        moved = []
+        for x in (k, v):
+            pool = torch.zeros(x.numel() + 8, dtype=x.dtype, device="cuda")
+            y = pool[shift:shift + x.numel()].view(x.shape)
+            y.copy_(x)
+            moved.append(y)
+        cache = N.PagedKVCache(*moved, pm, 1e4, N.V_TRANSPOSED if vt else N.V_ROWMAJOR)
+        outs.append(N.suffix_attn(q, cache, 0, n_past))
+        torch.cuda.synchronize()
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))

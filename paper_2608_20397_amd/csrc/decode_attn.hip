@@ -32,6 +32,7 @@
 #include "launch_decode.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace nexus {
 
@@ -130,9 +131,10 @@ __device__ __forceinline__ void store_empty(const DecodeArgs &a, int row, int sl
 // ---- pages shared between sequences (a warm prefix).  Consecutive sequences form groups of up to
 // kMaxGroupSeqs; a group's representative is its first sequence with a whole page.  Page p of
 // sequence j counts as shared when it is whole in j and in the representative and both map it to
-// one physical page (the representative's own pages all do); those pages are read once for all
-// the group's queries, every other page by its sequence alone.  A group whose representative's
-// first page is mapped by no other sequence shares nothing: one look at that page settles it.
+// one physical page; a page of the representative counts when another sequence's does.  Those pages
+// are read once for all the group's queries, every other page by its sequence alone.  A group whose
+// representative's first page is mapped by no other sequence shares nothing: one look at that page
+// settles it.
 struct GroupState {
   int b0, n;          // first sequence, sequences
   int rep;            // representative (index in the group)
@@ -165,6 +167,26 @@ __device__ __forceinline__ int group_lane_seq(const DecodeArgs &a, int g, int j)
 // 16-query column blocks of a wave that serves shared pages.
 __host__ __device__ constexpr int shared_blocks(int head_dim) { return head_dim == 256 ? 2 : 3; }
 
+// Place in a list of n entries that a thread's entry takes if it is appended, in thread order; n grows by
+// the workgroup's entries.  Called by the whole workgroup; it holds barriers, the last of them after every
+// thread has read the counts.
+__device__ __forceinline__ int place(bool take, int &n, int32_t *wave_cnt) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t m = __builtin_amdgcn_ballot_w64(take);
+  if (lane == 0) wave_cnt[wave] = __popcll(m);
+  __syncthreads();
+  int at = n;
+#pragma unroll
+  for (int w = 0; w < kDecWaves; ++w) {
+    const int c = wave_cnt[w];
+    if (w < wave) at += c;
+    n += c;
+  }
+  __syncthreads();
+  return at + __popcll(m & ((1ull << lane) - 1));
+}
+
 // Pages of one range of a group's representative, for the query heads hg of all the group's
 // sequences: one 16-query column block holds 16 / G sequences (one when G > 16), the group's column
 // blocks are dealt to the 4 waves and every wave reads every page.  Page pairs travel global -> LDS
@@ -196,7 +218,7 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
   const int per_block = a.group >= 16 ? 1 : 16 / a.group;
   const int n_blocks = (gs.n + per_block - 1) / per_block;
   const int p_lo = range * a.shared_split_pages;
-  const int n_pages = min(a.shared_split_pages, gs.rep_full - p_lo);
+  int n_pages = min(a.shared_split_pages, gs.rep_full - p_lo);
   const int slot = a.own_splits + range;
   // row of query column qn of column block cb: head g_lo + qn % g_cnt of sequence
   // cb * per_block + qn / g_cnt of the group; -1: none
@@ -236,6 +258,41 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
         reinterpret_cast<uint8_t *>(msk)[4 * i + wave] = (uint8_t)m;
       }
     }
+  }
+  // ---- the list: pages that every sequence of the group shares, then those that some share
+  const uint32_t all = 0xFFFFFFFFu >> (32 - gs.n);
+  const int n_range = n_pages;
+  int n_all = 0, n_list = 0;
+  {
+    constexpr int NU = kMaxSharedPages / 256;
+    int32_t phys[NU];
+    uint32_t mask[NU];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int i = min(tid + 256 * u, n_pages - 1);
+      phys[u] = pgs[i];
+      mask[u] = msk[i];
+    }
+#pragma unroll
+    for (int some = 0; some < 2; ++some) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        if (256 * u >= n_range) break;
+        const bool take = tid + 256 * u < n_range && __popc(mask[u]) >= 2 && (mask[u] != all) == some;
+        const int i = place(take, n_list, reinterpret_cast<int32_t *>(smem));   // ends in a barrier
+        if (take) {
+          pgs[i] = phys[u];
+          msk[i] = mask[u];
+        }
+      }
+      if (!some) n_all = n_list;
+    }
+  }
+  n_pages = n_list;
+  if (n_pages == 0) {
+    for (int cb = wave; cb < n_blocks; cb += kDecWaves) store_empty(a, row_of(cb), slot, grp);
+    return;
   }
   // ---- queries of this wave's column blocks wave, wave + 4, ...: B operands
   u32x4 qreg[NCB][KS];
@@ -298,15 +355,23 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
   }
 #pragma unroll
   for (int i = 0; i < kSharedStages - 1; ++i) issue(i);
-  for (int i = 0; i < n_pairs; ++i) {
+  // One pair.  EACH: some sequence of the group maps a page of it elsewhere.  Its column's scores of that
+  // page become -inf, and its outputs keep away from the page's values, because a probability of 0
+  // does not keep out an infinity or a NaN among them (0 x inf): such pairs are taken a page at a time
+  // (16 keys) into fresh accumulators, added to the columns that map the page.
+  auto pair = [&](int i, auto each) {
+    constexpr bool EACH = decltype(each)::value;
     wait_vm<NI *(kSharedStages - 2)>();   // this wave's part of pair i has landed
     tile_barrier();                       // all parts have, and the slot filled next is read out
     issue(i + kSharedStages - 1);
-    if (my_blocks == 0) continue;
+    if (my_blocks == 0) return;
     const char *kt = smem + (i & (kSharedStages - 1)) * STAGEB;
     const char *vt = kt + PAGEB;
-    const uint32_t mask0 = msk[2 * i];
-    const uint32_t mask1 = 2 * i + 1 < n_pages ? msk[2 * i + 1] : 0u;
+    uint32_t mask0 = 0, mask1 = 0;
+    if constexpr (EACH) {
+      mask0 = msk[2 * i];
+      mask1 = 2 * i + 1 < n_pages ? msk[2 * i + 1] : 0u;
+    }
     f32x4 s[NCB][2];
 #pragma unroll
     for (int c = 0; c < NCB; ++c)
@@ -324,7 +389,7 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
           s[c][pp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
               ka, __builtin_bit_cast(bf16x8, qreg[c][st]), s[c][pp], 0, 0, 0);
       }
-    bf16x8 pb[NCB];
+    u32x4 pb[NCB];
 #pragma unroll
     for (int c = 0; c < NCB; ++c) {
       float x[8];
@@ -332,7 +397,7 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
       for (int e = 0; e < 8; ++e) {
         const float r = s[c][e >> 2][e & 3];
         const float v = CAP ? a.cap_out * tanh_fast(r * a.cap_in) : r * a.scale_log2;
-        x[e] = ((e < 4 ? mask0 : mask1) & bit[c]) ? v : -INFINITY;
+        x[e] = !EACH || ((e < 4 ? mask0 : mask1) & bit[c]) ? v : -INFINITY;
       }
       float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])),
                        fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
@@ -354,7 +419,7 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
         w[e] = pack_bf16x2(fast_exp2(x[2 * e] - nm), fast_exp2(x[2 * e + 1] - nm));
         lsum[c] += __uint_as_float(w[e] << 16) + __uint_as_float(w[e] & 0xFFFF0000u);
       }
-      pb[c] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
+      pb[c] = u32x4{w[0], w[1], w[2], w[3]};
     }
 #pragma unroll
     for (int t = 0; t < DT; ++t) {
@@ -371,10 +436,29 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
         va = tr_read_pair(p0, p0 + 2 * PAGEB);
       }
 #pragma unroll
-      for (int c = 0; c < NCB; ++c)
-        o[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb[c], o[c][t], 0, 0, 0);
+      for (int c = 0; c < NCB; ++c) {
+        if constexpr (!EACH) {
+          o[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, __builtin_bit_cast(bf16x8, pb[c]),
+                                                            o[c][t], 0, 0, 0);
+        } else {
+          const u32x4 v = __builtin_bit_cast(u32x4, va);
+#pragma unroll
+          for (int pp = 0; pp < 2; ++pp) {
+            const f32x4 x = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                __builtin_bit_cast(s16x4, u32x2{v[2 * pp], v[2 * pp + 1]}),
+                __builtin_bit_cast(s16x4, u32x2{pb[c][2 * pp], pb[c][2 * pp + 1]}),
+                f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            const bool in = (pp ? mask1 : mask0) & bit[c];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[c][t][e] += in ? x[e] : 0.f;
+          }
+        }
+      }
     }
-  }
+  };
+  int i = 0;
+  for (; i < n_all >> 1; ++i) pair(i, std::false_type{});
+  for (; i < n_pairs; ++i) pair(i, std::true_type{});
   wait_vm<0>();      // no DMA may land once the ring is used for something else
 #pragma unroll
   for (int c = 0; c < NCB; ++c) {
@@ -389,30 +473,17 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
 template <typename F>
 __device__ __forceinline__ int build_list(int p_lo, int p_hi, int32_t *pgs, uint16_t *lps,
                                           int32_t *wave_cnt, F pick) {
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int n = 0;
   for (int base = p_lo; base < p_hi; base += 256) {
     const int p = base + threadIdx.x;
     const int32_t phys = p < p_hi ? pick(p) : -1;
-    const uint64_t m = __builtin_amdgcn_ballot_w64(phys >= 0);
-    if (lane == 0) wave_cnt[wave] = __popcll(m);
-    __syncthreads();
-    int at = n, total = 0;
-#pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) {
-      const int c = wave_cnt[w];
-      if (w < wave) at += c;
-      total += c;
-    }
+    const int i = place(phys >= 0, n, wave_cnt);
     if (phys >= 0) {
-      const int i = at + __popcll(m & ((1ull << lane) - 1));
       pgs[i] = phys;
       lps[i] = (uint16_t)(p - p_lo);
     }
-    n += total;
-    __syncthreads();
   }
+  __syncthreads();
   return n;
 }
 
@@ -441,6 +512,7 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qn = lane & 15, grp = lane >> 4;
   int b, hg, split, len;
+  int own_full = 0;        // lane j: whole pages of sequence j of the own group
   GroupState own{};
   if constexpr (SH) {
     // splits vary slowest: the first ids hold the sequences' first pages, which a shared prefix
@@ -470,6 +542,7 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
       if (job == id) {
         own = group_state(a, own_g, lane_len >> 4, page0, 32);
         len = __builtin_amdgcn_readlane(lane_len, 32 + b - own.b0);
+        own_full = __shfl(lane_len >> 4, 32 + (lane & 31));
         if (split == 0 && hg == 0 && tid == 0) a.flags[b] = own.shares;
       }
       if (job >= n_jobs) break;
@@ -528,7 +601,21 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
     const int n_shared = min(len >> 4, own.rep_full);
     n_sp = build_list(p_begin, p_end, pgs, lps, reinterpret_cast<int32_t *>(smem), [&](int p) {
       const int32_t mine = map[p];
-      return mine == rep[p] && p < n_shared ? -1 : mine;
+      if (b != own.b0 + own.rep) return mine == rep[p] && p < n_shared ? -1 : mine;
+      // the representative's page is a shared one if any other sequence maps it
+      bool found = false;
+      for (int j0 = 0; j0 < own.n && __builtin_amdgcn_ballot_w64(!found && p < n_shared); j0 += 8) {
+        int32_t x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          x[e] = a.maps[(size_t)(own.b0 + min(j0 + e, own.n - 1)) * a.map_stride + p];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int full = __builtin_amdgcn_readlane(own_full, min(j0 + e, own.n - 1));
+          found |= j0 + e != own.rep && p < full && x[e] == mine;
+        }
+      }
+      return found && p < n_shared ? -1 : mine;
     });
     if (n_sp == 0) {
       if (wave == 0 && qn < g_cnt) store_empty(a, b * a.n_q_heads + hq0 + qn, split, grp);

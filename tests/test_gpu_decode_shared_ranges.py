@@ -1,0 +1,99 @@
+"""GPU parity of the decode step over physical pages that sequences share, at lengths for which the launch
+takes them together (512 MB of keys and values or more), against the fp64 oracle on sampled sequences;
+tolerances as the other decode tests.  The shared pages span many ranges.
+
+A value that is not finite belongs to the sequences that map its page: every other sequence of the
+batch must come out as if it were not there."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2608_20397_amd import nexus as N
+from synth import PAGE
+
+from test_gpu_decode import _check
+
+pytestmark = pytest.mark.gpu
+
+
+class Batch:
+    """Sequences of lens[b] tokens over one pool; those listed in share = [(sequences, pages)] map the first
+    pages of the first of them, except the (sequence, page) pairs of `moved`."""
+
+    def __init__(self, d, kv, g, lens, share, layout="rowmajor", cap=0.0, moved=(), seed=1):
+        self.layout, self.cap, self.lens = layout, cap, list(lens)
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(seed)
+        pages = [-(-n // PAGE) for n in lens]
+        first = np.cumsum([0] + pages)
+        maps = np.zeros((len(lens), max(pages)), dtype=np.int64)
+        for b, n in enumerate(pages):
+            maps[b, :n] = first[b] + np.arange(n)
+        for seqs, n in share:
+            for b in seqs[1:]:
+                keep = [p for p in range(min(n, lens[b] // PAGE)) if (b, p) not in moved]
+                maps[b, keep] = maps[seqs[0], keep]
+        used = np.unique(np.concatenate([maps[b, :n] for b, n in enumerate(pages)]))
+        place = np.random.default_rng(seed).permutation(len(used))
+        self.maps = place[np.searchsorted(used, maps).clip(max=len(used) - 1)].astype(np.int32)
+        npp = len(used)
+        normal = lambda shape, std: (torch.randn(shape, generator=gen, device="cuda") * std).bfloat16()
+        self.k = normal((1, npp, kv, PAGE, d), 2 * d ** -0.5)
+        self.v = normal((1, kv, d, npp * PAGE) if layout == "transposed" else self.k.shape, 1.0)
+        self.q = normal((len(lens), kv * g, d), 1.0)
+        self.bytes = sum(lens) * kv * d * 4
+
+    def values(self, b, p):
+        """V of sequence b's page p, every head."""
+        phys = int(self.maps[b, p])
+        if self.layout == "transposed":
+            return self.v[0, :, :, phys * PAGE:(phys + 1) * PAGE]
+        return self.v[0, phys]
+
+    def run(self, **kw):
+        cache = N.PagedKVCache(self.k, self.v, torch.zeros(1, dtype=torch.int32, device="cuda"), 1e4,
+                               N.V_TRANSPOSED if self.layout == "transposed" else N.V_ROWMAJOR)
+        out = N.decode_attn(self.q, cache, torch.from_numpy(self.maps).cuda(),
+                            torch.tensor(self.lens, dtype=torch.int32, device="cuda"), max(self.lens),
+                            0, softcap=self.cap, **kw)
+        torch.cuda.synchronize()
+        return out.float().cpu().double().numpy()
+
+    def oracle(self, seqs):
+        f64 = lambda x: x.float().cpu().double().numpy()
+        return O.decode_attention(f64(self.q)[seqs], f64(self.k[0]), f64(self.v[0]), self.maps[seqs],
+                                  [self.lens[b] for b in seqs], PAGE, self.layout, softcap=self.cap)
+
+
+SHAPES = [
+    # head_dim, KV heads, query heads per KV head, V layout, cap, sequences, tokens, shared pages
+    (128, 8, 5, "rowmajor", 0.0, 9, 15000, 800),
+    (256, 8, 2, "transposed", 50.0, 6, 11200, 650),
+    (64, 2, 32, "rowmajor", 0.0, 16, 66200, 4096),
+    (128, 8, 3, "transposed", 0.0, 17, 8200, 333),
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"d{s[0]}-{s[3]}")
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_nonfinite_values_stay_with_their_sequences(shape, bad):
+    d, kv, g, layout, cap, n, tokens, shared = shape
+    lens = [tokens - 37 * b for b in range(n)]
+    # page 40 is shared by the first two sequences alone, page 41 by the last two
+    moved = [(b, 40) for b in range(2, n)] + [(b, 41) for b in range(1, n)]
+    t = Batch(d, kv, g, lens, [(range(n), shared)], layout, cap, moved)
+    t.maps[n - 2, 41] = t.maps[n - 1, 41]
+    assert t.bytes >= 512 << 20
+    print(f"decode {shape}: values {bad}", flush=True)
+    hit = [0, 1, 3]
+    t.values(0, shared + 3)[:] = bad           # private to the first sequence, behind the prefix
+    t.values(3, shared + 1)[:] = bad           # to a later one
+    t.values(0, 40)[:] = bad                   # of the first two
+    got = t.run()
+    assert not np.isfinite(got[hit]).any()
+    others = [b for b in range(n) if b not in hit]
+    assert np.isfinite(got[others]).all()
+    sel = [2, others[len(others) // 2], n - 1]
+    _check(got[sel], t.oracle(sel), "bf16", f"{shape}")

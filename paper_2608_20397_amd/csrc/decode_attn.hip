@@ -727,6 +727,7 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
                                                         __builtin_bit_cast(s16x4, u32x2{w[0], w[1]}),
                                                         acc, 0, 0, 0);
     };
+    // (a page alone: the values beside it are zeros, for 0 x inf is NaN)
     if constexpr (!VT) {
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp)
@@ -735,7 +736,8 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
           const int byte = 16 * lane + 1024 * j;
           const int row = byte / ROWB, c = (byte % ROWB) >> 4;
           *reinterpret_cast<u32x4 *>(vstage + pp * 16 * ROWB + row * ROWB +
-                                     16 * (c ^ vswz<D>(row))) = pr.pg[pp].v[j];
+                                     16 * (c ^ vswz<D>(row))) =
+              pp == 0 || two ? pr.pg[pp].v[j] : u32x4{0u, 0u, 0u, 0u};
         }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -758,7 +760,7 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
       u32x2 m[NP];
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp) {
-        const int keep = len - key[pp];
+        const int keep = pp == 0 || two ? len - key[pp] : 0;
         m[pp][0] = keep >= 2 ? 0xFFFFFFFFu : keep == 1 ? 0x0000FFFFu : 0u;
         m[pp][1] = keep >= 4 ? 0xFFFFFFFFu : keep == 3 ? 0x0000FFFFu : 0u;
       }

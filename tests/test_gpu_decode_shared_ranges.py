@@ -97,3 +97,20 @@ def test_nonfinite_values_stay_with_their_sequences(shape, bad):
     assert np.isfinite(got[others]).all()
     sel = [2, others[len(others) // 2], n - 1]
     _check(got[sel], t.oracle(sel), "bf16", f"{shape}")
+
+
+@pytest.mark.parametrize("d,layout", [(64, "rowmajor"), (128, "rowmajor"), (128, "transposed"),
+                                      (256, "rowmajor")])
+@pytest.mark.parametrize("pages", [1, 4, 5, 33])
+def test_infinite_value_in_a_page_without_a_pair(d, layout, pages):
+    """Pages are taken two at a time: an odd one's infinity comes out as the infinity it is."""
+    t = Batch(d, 2, 3, [PAGE * pages], [], layout)
+    for p in range(pages):
+        v = t.values(0, p).clone()
+        if layout == "transposed":
+            t.values(0, p)[:, 5, 3] = float("inf")
+        else:
+            t.values(0, p)[:, 3, 5] = float("inf")
+        got = t.run()
+        assert np.isposinf(got[..., 5]).all(), p
+        t.values(0, p)[:] = v

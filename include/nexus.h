@@ -262,11 +262,16 @@ size_t nexus_suffix_attn_varlen_workspace(int32_t n_seqs, const int32_t *q_start
  *               chosen from n_seqs, the head counts and max_seq_len, merged by a second kernel.
  *   layer, softcap, v_layout, scale: as nexus_suffix_attn (same checks, same head_dim limits).
  *   out         [n_seqs][n_q_heads][head_dim] of the cache dtype.
- *   workspace   at least nexus_decode_attn_workspace() bytes (NULL allowed when that is 0);
- *               contents on entry do not matter.
+ *   workspace   nexus_decode_attn_workspace() bytes (NULL allowed when that is 0); contents on
+ *               entry do not matter.
  *               Where the bound allows 512 MB of keys and values or more, bf16 launches look for
  *               physical pages that sequences share (a warm prefix, from page 0 on) and read those
- *               once for the sequences that map them.
+ *               once for the sequences that map them.  The partial results of those pages are
+ *               most of the workspace, and with fewer sequences they may take more than with more.
+ *               A smaller buffer is accepted down to the partials of the sequences' own pages,
+ *               n_seqs * n_q_heads * splits * (head_dim + 2) * 4 bytes (0 for one split;
+ *               NEXUS_EWORKSPACE below that): the shared pages are then cut into fewer ranges, or not
+ *               looked for.  So one buffer of the largest batch serves the smaller ones.
  * bf16 caches: each workgroup reads a KV head's keys and values once for up to 16 query heads
  * (MFMA, fp32 accumulation, probabilities rounded to bf16 as in nexus_suffix_attn).  f32 caches:
  * fp32 VALU kernel.
@@ -277,7 +282,8 @@ nexus_status nexus_decode_attn(const void *q, int32_t n_seqs, int32_t n_q_heads,
                                int32_t layer, float softcap, int32_t v_layout, float scale,
                                void *out, void *workspace, size_t workspace_bytes, void *stream);
 
-/* Workspace bytes nexus_decode_attn needs (0 if none, SIZE_MAX if the arguments are invalid). */
+/* Workspace bytes with which nexus_decode_attn does all it can (0 if none, SIZE_MAX if the arguments are
+ * invalid). */
 size_t nexus_decode_attn_workspace(int32_t n_seqs, int32_t n_q_heads, const nexus_kv_cache *cache,
                                    int32_t max_seq_len);
 

@@ -31,6 +31,8 @@
 #include "attn_dma.h"
 #include "launch_decode.h"
 
+#include <stdint.h>
+
 #include <algorithm>
 #include <type_traits>
 
@@ -1087,7 +1089,19 @@ struct DecodeShape {
   int slots() const { return own_splits + (n_groups ? shared_splits : 0); }
 };
 
-DecodeShape decode_shape(const DecodeLaunch &p) {
+// Workspace bytes of `slots` partials a row.
+size_t part_bytes(const DecodeLaunch &p, int64_t slots) {
+  return (size_t)p.n_seqs * p.n_q_heads * slots * (p.head_dim + 2) * sizeof(float);
+}
+size_t shape_bytes(const DecodeLaunch &p, const DecodeShape &s) {
+  if (s.slots() <= 1) return 0;
+  return part_bytes(p, s.slots()) + (s.n_groups ? (size_t)p.n_seqs * sizeof(int32_t) : 0);
+}
+
+// The shape that fits a workspace of ws_bytes: the splits of the sequences' own pages always do (the
+// call is refused otherwise), shared pages are cut into as many ranges as it holds partials for, and not
+// looked for where it holds too few.
+DecodeShape decode_shape(const DecodeLaunch &p, size_t ws_bytes) {
   DecodeShape s{};
   const int group = p.n_q_heads / p.n_kv_heads;
   // bf16: one workgroup per 16 query heads of a group; f32: one wave per query head
@@ -1104,15 +1118,19 @@ DecodeShape decode_shape(const DecodeLaunch &p) {
   // sequences per group: what the column blocks of a workgroup hold
   const int per_block = group >= 16 ? 1 : 16 / group;
   const int cap = std::min(kMaxGroupSeqs, kDecWaves * shared_blocks(p.head_dim) * per_block);
-  s.n_groups = (p.n_seqs + cap - 1) / cap;
-  s.group_seqs = (p.n_seqs + s.n_groups - 1) / s.n_groups;
-  s.n_groups = (p.n_seqs + s.group_seqs - 1) / s.group_seqs;
+  const int n_groups = (p.n_seqs + cap - 1) / cap;
+  s.group_seqs = (p.n_seqs + n_groups - 1) / n_groups;
   // about one job of shared pages per CU
-  const int64_t heads = (int64_t)s.n_groups * p.n_kv_heads * per_kv;
-  const int64_t ns = heads < 256 ? 256 / heads : 1;
+  const int64_t heads = (int64_t)((p.n_seqs + s.group_seqs - 1) / s.group_seqs) * p.n_kv_heads * per_kv;
+  int64_t ns = heads < 256 ? 256 / heads : 1;
+  const size_t fixed = part_bytes(p, s.own_splits) + (size_t)p.n_seqs * sizeof(int32_t);
+  const int64_t fit = ws_bytes > fixed ? (int64_t)((ws_bytes - fixed) / part_bytes(p, 1)) : 0;
+  if (fit * kMaxSharedPages < max_pages) return s;
+  ns = std::min(ns, fit);
   int64_t sp = (max_pages + ns - 1) / ns;
   if (sp < 16) sp = 16;
   if (sp > kMaxSharedPages) sp = kMaxSharedPages;
+  s.n_groups = (p.n_seqs + s.group_seqs - 1) / s.group_seqs;
   s.shared_split_pages = (int)sp;
   s.shared_splits = (int)((max_pages + s.shared_split_pages - 1) / s.shared_split_pages);
   return s;
@@ -1120,17 +1138,14 @@ DecodeShape decode_shape(const DecodeLaunch &p) {
 
 }  // namespace
 
-size_t decode_workspace_bytes(const DecodeLaunch &p) {
-  const DecodeShape s = decode_shape(p);
-  if (s.slots() <= 1) return 0;
-  return (size_t)p.n_seqs * p.n_q_heads * s.slots() * (p.head_dim + 2) * sizeof(float) +
-         (s.n_groups ? (size_t)p.n_seqs * sizeof(int32_t) : 0);
-}
+size_t decode_workspace_bytes(const DecodeLaunch &p) { return shape_bytes(p, decode_shape(p, SIZE_MAX)); }
+
+size_t decode_workspace_min(const DecodeLaunch &p) { return shape_bytes(p, decode_shape(p, 0)); }
 
 hipError_t launch_decode(const DecodeLaunch &p, hipStream_t stream) {
   const int group = p.n_q_heads / p.n_kv_heads;
   const int n_qgroups = (group + 15) / 16;
-  DecodeShape sh = decode_shape(p);
+  DecodeShape sh = decode_shape(p, p.workspace_bytes);
   // shared pages travel by LDS DMA, 16 aligned bytes a lane: a cache that starts elsewhere is read
   // sequence by sequence
   if ((uintptr_t)p.cache_k % 16 != 0 || (uintptr_t)p.cache_v % 16 != 0) sh.n_groups = 0;

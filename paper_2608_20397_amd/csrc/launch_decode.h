@@ -21,12 +21,15 @@ struct DecodeLaunch {
   float scale;              // resolved (never 0)
   float softcap;            // 0 = off
   void *workspace;
+  size_t workspace_bytes;
 };
 
 // Pages per key split of a decode launch (fixed by the shape, not by the device lengths).
 int decode_split_pages(int32_t n_seqs, int32_t n_kv_heads, int32_t wgs_per_kv_head,
                        int32_t max_len);
+// Workspace bytes with which a launch does all it can, and without which it cannot run.
 size_t decode_workspace_bytes(const DecodeLaunch &p);
+size_t decode_workspace_min(const DecodeLaunch &p);
 hipError_t launch_decode(const DecodeLaunch &p, hipStream_t stream);
 
 // Token-range copy between two page maps of one cache (all layers, K and V); optionally also

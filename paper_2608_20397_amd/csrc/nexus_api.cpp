@@ -568,9 +568,10 @@ nexus_status nexus_decode_attn(const void *q, int32_t n_seqs, int32_t n_q_heads,
   nexus_status st = prepare_decode(q, n_seqs, n_q_heads, cache, maps, map_stride, seq_len,
                                    max_seq_len, layer, softcap, v_layout, scale, out, L);
   if (st) return st;
-  const size_t need = decode_workspace_bytes(L);
+  const size_t need = decode_workspace_min(L);
   if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return NEXUS_EWORKSPACE;
   L.workspace = workspace;
+  L.workspace_bytes = workspace ? workspace_bytes : 0;
   return from_hip(launch_decode(L, as_stream(stream)));
 }
 

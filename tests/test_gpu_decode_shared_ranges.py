@@ -114,3 +114,39 @@ def test_infinite_value_in_a_page_without_a_pair(d, layout, pages):
         got = t.run()
         assert np.isposinf(got[..., 5]).all(), p
         t.values(0, p)[:] = v
+
+
+def test_one_workspace_for_all_smaller_batches():
+    """A buffer sized for the largest batch serves every smaller one, across the edge of a group (32
+    sequences) on both sides of which the shared pages' partials differ, and so does one that holds
+    nothing beside the partials of the sequences' own pages; one byte less than those is refused."""
+    d, kv, g, tokens = 128, 8, 5, 4400
+    for largest in (33, 48):
+        t = Batch(d, kv, g, [tokens] * largest, [(range(largest), 260)])
+        cache = N.PagedKVCache(t.k, t.v, torch.zeros(1, dtype=torch.int32, device="cuda"), 1e4)
+        size = lambda n: N.decode_attn_workspace_bytes(cache, n, kv * g, tokens)
+        buf = torch.empty(size(largest), dtype=torch.uint8, device="cuda")
+        if largest == 33:
+            assert size(32) > buf.numel()
+        full, maps, q = t.oracle(range(largest)), t.maps, t.q
+        for n in (2, 31, 32, 33, 48):
+            if n > largest:
+                continue
+            t.lens, t.maps, t.q = [tokens] * n, np.ascontiguousarray(maps[:n]), q[:n].contiguous()
+            for ws in (buf, buf[:_own_bytes(n, kv, g, d, tokens)]):
+                buf.fill_(0xFF)
+                _check(t.run(workspace=ws), full[:n], "bf16", f"{n} sequences, {ws.numel()} bytes")
+            with pytest.raises(N.NexusError) as e:
+                t.run(workspace=buf[:_own_bytes(n, kv, g, d, tokens) - 1])
+            assert e.value.status == N.EWORKSPACE
+
+
+def _own_bytes(n, kv, g, d, tokens):
+    """Partials of the sequences' own splits (tests of up to 256 workgroup pairs)."""
+    pages, pairs = -(-tokens // PAGE), n * kv
+    sp = max(-(-pages // -(-512 // pairs)), 32)
+    splits = -(-pages // sp)
+    if 256 < pairs * splits < 512 and pairs <= 256:
+        splits = 256 // pairs
+        splits = -(-pages // -(-pages // splits))
+    return n * kv * g * splits * (d + 2) * 4 if splits > 1 else 1

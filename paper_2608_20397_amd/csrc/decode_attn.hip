@@ -49,6 +49,7 @@ constexpr float kDecSlack = 6.0f;
 constexpr int kMaxDecSplits = 1024; // splits per sequence at most (bounds the merge's loop)
 constexpr int kMaxSplitPages = 2048;  // pages per split at most (page list in LDS)
 constexpr int kMaxSharedPages = 1024; // pages per shared range at most (page list and masks in LDS)
+constexpr int kMinRangePages = 16;    // and at least
 constexpr int kMaxGroupSeqs = 32;     // sequences whose shared pages one workgroup serves
 constexpr int64_t kSharedMinBytes = (int64_t)512 << 20;   // keys + values of all sequences
 constexpr int kSharedStages = 4;      // ring of page pairs in LDS (shared pages)
@@ -67,8 +68,9 @@ struct DecodeArgs {
   int32_t n_seqs;
   // shared pages (0 groups: none looked for): slots own_splits .. max_splits - 1 of a row belong
   // to the page ranges of its group
-  int32_t n_groups, group_seqs, shared_splits, shared_split_pages, own_splits;
-  int32_t *flags;         // [n_seqs]: whether a sequence's group shares pages (the merge's use)
+  int32_t n_groups, group_seqs, shared_splits, own_splits;
+  int32_t share_pages;    // whole pages from which on a sequence is long enough to share them
+  int32_t *flags;         // [n_seqs]: ranges of shared pages a sequence has partials of (the merge's use)
   uint32_t n_cols;        // transposed V: NPP * 16
   float scale_log2;       // scale * log2(e)
   float cap_in;           // scale / softcap
@@ -131,39 +133,63 @@ __device__ __forceinline__ void store_empty(const DecodeArgs &a, int row, int sl
 }
 
 // ---- pages shared between sequences (a warm prefix).  Consecutive sequences form groups of up to
-// kMaxGroupSeqs; a group's representative is its first sequence with a whole page.  Page p of
-// sequence j counts as shared when it is whole in j and in the representative and both map it to
-// one physical page; a page of the representative counts when another sequence's does.  Those pages
-// are read once for all the group's queries, every other page by its sequence alone.  A group whose
-// representative's first page is mapped by no other sequence shares nothing: one look at that page
-// settles it.
+// kMaxGroupSeqs.  Page p of two sequences of a group counts as shared when it is whole in both and both
+// map it to one physical page; such pages are read once for all the group's sharers, every other page by
+// its sequence alone.  To that end a page is compared with that of one sharer, the representative, whose
+// own page counts when any other sharer's does.
+// Whether a group shares is settled by looks at two pages, where it pays:
+//   * half of its sequences or more have share_pages whole pages, their part of kSharedMinBytes / 2; below
+//     that the caches serve the repeated reads, whatever the launch's bound (32 sequences of 500 tokens,
+//     256 of them shared, in a launch for 17473: 18 us, through the shared pages 43; of 2100 tokens, 1050
+//     shared: 49 and 40);
+//   * they share the first half: 32 sequences of 17473 tokens that share 4096, 6144, 8192, 12800 tokens take
+//     306, 275, 243, 202 us page by page and 322, 281, 243, 142 so.  The first look, at page
+//     share_pages / 2, costs nothing: it is loaded with the lengths;
+//   * every sequence that long shares, because one that does not takes as long as ever (31 of 32 sequences
+//     on a prefix, one private: 176 us page by page, 196 so; the first one alone: 171, 185).
 struct GroupState {
   int b0, n;          // first sequence, sequences
   int rep;            // representative (index in the group)
   int rep_full;       // its whole pages
-  bool shares;
+  uint32_t sharers;   // sequences that share pages (the representative first); 0: nothing is shared
+  int n_sh;           // their number
+  bool by_split;      // order of the workgroups: splits vary slowest
 };
-// Lane first + j of the wave's 32 lanes from `first` on holds the whole pages and the first page
-// of sequence j of group g.
-__device__ __forceinline__ GroupState group_state(const DecodeArgs &a, int g, int full,
-                                                  int32_t page0, int first) {
+// Lanes j and j + 32 hold the whole pages and page share_pages / 2 of sequence j of group g.
+__device__ __forceinline__ GroupState group_state(const DecodeArgs &a, int g, int full, int32_t page) {
   GroupState s;
   s.b0 = g * a.group_seqs;
   s.n = min(a.group_seqs, a.n_seqs - s.b0);
-  const uint64_t in_group = ((1ull << s.n) - 1) << first;      // n <= 32
-  const uint64_t holders = __builtin_amdgcn_ballot_w64(full > 0) & in_group;
-  const int rep_lane = holders ? __builtin_ctzll(holders) : first;
-  s.rep = rep_lane - first;
-  s.rep_full = holders ? __builtin_amdgcn_readlane(full, rep_lane) : 0;
-  const int32_t phys = __builtin_amdgcn_readlane(page0, rep_lane);
-  const uint64_t same = __builtin_amdgcn_ballot_w64(full > 0 && page0 == phys) & in_group;
-  s.shares = __popcll(same) >= 2;
+  const int j = threadIdx.x & 31;
+  auto which = [&](bool x) { return (uint32_t)__builtin_amdgcn_ballot_w64(x && j < s.n); };
+  s.by_split = 2 * __popc(which(2 * (int64_t)full <= (int64_t)a.own_splits * a.split_pages)) > s.n;
+  s.rep = s.rep_full = s.n_sh = 0;
+  s.sharers = 0;
+  const uint32_t large = which(full >= a.share_pages);
+  if (__popc(large) < max(2, (s.n + 1) / 2)) return s;
+  s.rep = __builtin_ctz(large);
+  s.rep_full = __builtin_amdgcn_readlane(full, s.rep);
+  if (large & ~which(page == __builtin_amdgcn_readlane(page, s.rep))) return s;
+  const int half = s.rep_full / 2;
+  const uint32_t longer = which(full > half);
+  const int32_t x = a.maps[(size_t)(s.b0 + min(j, s.n - 1)) * a.map_stride + half];
+  if (__popc(longer) < 2 || longer & ~which(x == __builtin_amdgcn_readlane(x, s.rep))) return s;
+  s.sharers = longer;
+  s.rep = __builtin_ctz(longer);
+  s.rep_full = __builtin_amdgcn_readlane(full, s.rep);
+  s.n_sh = __popc(longer);
+  s.by_split = true;
   return s;
 }
-// Sequence whose length and first page a lane loads for group g (index clamped to the group).
-__device__ __forceinline__ int group_lane_seq(const DecodeArgs &a, int g, int j) {
-  const int b0 = g * a.group_seqs;
-  return b0 + min(j, min(a.group_seqs, a.n_seqs - b0) - 1);
+
+// Ranges that a group's shared pages are cut into and pages of each: one for each workgroup of the
+// sharers (per KV head and query group), up to the partial slots, at least kMinRangePages pages.  Every
+// sequence has a workgroup for each 2048 pages and a group two sharers, so no workgroup has two ranges.
+__device__ __forceinline__ void shared_ranges(const DecodeArgs &a, const GroupState &gs, int &n_ranges,
+                                              int &range_pages) {
+  const int n = min(a.shared_splits, gs.n_sh * a.own_splits);
+  range_pages = min(max((gs.rep_full + n - 1) / n, kMinRangePages), kMaxSharedPages);
+  n_ranges = (gs.rep_full + range_pages - 1) / range_pages;
 }
 
 // 16-query column blocks of a wave that serves shared pages.
@@ -189,8 +215,8 @@ __device__ __forceinline__ int place(bool take, int &n, int32_t *wave_cnt) {
   return at + __popcll(m & ((1ull << lane) - 1));
 }
 
-// Pages of one range of a group's representative, for the query heads hg of all the group's
-// sequences: one 16-query column block holds 16 / G sequences (one when G > 16), the group's column
+// The shared pages of one range (the representative's pages p_lo .. + n_range - 1), for the query heads hg
+// of the group's sharers: one 16-query column block holds 16 / G of them (one when G > 16), the column
 // blocks are dealt to the 4 waves and every wave reads every page.  Page pairs travel global -> LDS
 // through a ring of kSharedStages pairs (LDS DMA; wave w fills K (w even) or V (w odd) of page w / 2
 // of the pair), one barrier per pair; per pair a wave forms S^T with 16x16x32 MFMAs, masks the
@@ -203,8 +229,8 @@ __device__ __forceinline__ int place(bool take, int &n, int32_t *wave_cnt) {
 // 184 -> 58 us a call.
 template <int D, bool VT, bool CAP>
 __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupState &gs, int lane_full,
-                                             int hg, int range, char *smem, int32_t *pgs,
-                                             uint32_t *msk) {
+                                             int hg, int p_lo, int n_range, int slot, char *smem,
+                                             int32_t *pgs, uint32_t *msk, const int32_t *ranks) {
   constexpr int NCB = shared_blocks(D);
   constexpr int KS = D / 32, DT = D / 16, KCH = D / 8;
   constexpr int ROWB = 2 * D;
@@ -218,32 +244,25 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
   const int h = hg / a.n_qgroups, g_lo = hg % a.n_qgroups * 16;
   const int g_cnt = min(16, a.group - g_lo);
   const int per_block = a.group >= 16 ? 1 : 16 / a.group;
-  const int n_blocks = (gs.n + per_block - 1) / per_block;
-  const int p_lo = range * a.shared_split_pages;
-  int n_pages = min(a.shared_split_pages, gs.rep_full - p_lo);
-  const int slot = a.own_splits + range;
-  // row of query column qn of column block cb: head g_lo + qn % g_cnt of sequence
-  // cb * per_block + qn / g_cnt of the group; -1: none
+  const int n_blocks = (gs.n_sh + per_block - 1) / per_block;
+  // row of query column qn of column block cb: head g_lo + qn % g_cnt of sharer
+  // cb * per_block + qn / g_cnt; -1: none
   const int in_block = qn / g_cnt;
   auto seq_of = [&](int cb) {
-    const int j = cb * per_block + in_block;
-    return in_block < per_block && j < gs.n ? j : -1;
+    const int r = cb * per_block + in_block;
+    return in_block < per_block && r < gs.n_sh ? ranks[r] : -1;
   };
   auto row_of = [&](int cb) {
     const int j = seq_of(cb);
     return j < 0 ? -1 : (gs.b0 + j) * a.n_q_heads + h * a.group + g_lo + qn - in_block * g_cnt;
   };
-  if (n_pages <= 0) {
-    for (int cb = wave; cb < n_blocks; cb += kDecWaves) store_empty(a, row_of(cb), slot, grp);
-    return;
-  }
 
   // ---- the range's physical pages and, per page, the sequences that share it: lane = page, wave w
   // takes sequences 8 w .. 8 w + 7 (byte w of the page's mask)
   {
     const int32_t *rep = a.maps + (size_t)(gs.b0 + gs.rep) * a.map_stride + p_lo;
-    for (int i0 = 0; i0 < n_pages; i0 += 64) {
-      const int i = i0 + lane, ic = min(i, n_pages - 1);
+    for (int i0 = 0; i0 < n_range; i0 += 64) {
+      const int i = i0 + lane, ic = min(i, n_range - 1);
       const int32_t phys = rep[ic];
       int32_t x[8];
 #pragma unroll
@@ -253,18 +272,16 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int full = __builtin_amdgcn_readlane(lane_full, 8 * wave + e);
-        if (8 * wave + e < gs.n && p_lo + i < full && x[e] == phys) m |= 1u << e;
+        if ((gs.sharers >> (8 * wave + e) & 1) && p_lo + i < full && x[e] == phys) m |= 1u << e;
       }
-      if (i < n_pages) {
+      if (i < n_range) {
         if (wave == 0) pgs[i] = phys;
         reinterpret_cast<uint8_t *>(msk)[4 * i + wave] = (uint8_t)m;
       }
     }
   }
-  // ---- the list: pages that every sequence of the group shares, then those that some share
-  const uint32_t all = 0xFFFFFFFFu >> (32 - gs.n);
-  const int n_range = n_pages;
-  int n_all = 0, n_list = 0;
+  // ---- the list: pages of all the sharers, then those that two or more of them map
+  int n_all = 0, n_pages = 0;
   {
     constexpr int NU = kMaxSharedPages / 256;
     int32_t phys[NU];
@@ -272,7 +289,7 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      const int i = min(tid + 256 * u, n_pages - 1);
+      const int i = min(tid + 256 * u, n_range - 1);
       phys[u] = pgs[i];
       mask[u] = msk[i];
     }
@@ -281,17 +298,17 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
 #pragma unroll
       for (int u = 0; u < NU; ++u) {
         if (256 * u >= n_range) break;
-        const bool take = tid + 256 * u < n_range && __popc(mask[u]) >= 2 && (mask[u] != all) == some;
-        const int i = place(take, n_list, reinterpret_cast<int32_t *>(smem));   // ends in a barrier
+        const bool take = tid + 256 * u < n_range && __popc(mask[u]) >= 2 &&
+                          (mask[u] != gs.sharers) == some;
+        const int i = place(take, n_pages, reinterpret_cast<int32_t *>(smem));   // ends in a barrier
         if (take) {
           pgs[i] = phys[u];
           msk[i] = mask[u];
         }
       }
-      if (!some) n_all = n_list;
+      if (!some) n_all = n_pages;
     }
   }
-  n_pages = n_list;
   if (n_pages == 0) {
     for (int cb = wave; cb < n_blocks; cb += kDecWaves) store_empty(a, row_of(cb), slot, grp);
     return;
@@ -357,7 +374,7 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
   }
 #pragma unroll
   for (int i = 0; i < kSharedStages - 1; ++i) issue(i);
-  // One pair.  EACH: some sequence of the group maps a page of it elsewhere.  Its column's scores of that
+  // One pair.  EACH: some sharer maps a page of it elsewhere.  Its columns' scores of that
   // page become -inf, and its outputs keep away from the page's values, because a probability of 0
   // does not keep out an infinity or a NaN among them (0 x inf): such pairs are taken a page at a time
   // (16 keys) into fresh accumulators, added to the columns that map the page.
@@ -470,27 +487,23 @@ __device__ __forceinline__ void shared_pages(const DecodeArgs &a, const GroupSta
   }
 }
 
-// Appends the pages p_lo + i of [p_lo, p_hi) that `pick` gives a physical page >= 0 for to the lists
-// (physical page, i), in page order; returns the list length.  Called by the whole workgroup.
+// List of the physical pages >= 0 that `pick` gives for pages [p_lo, p_hi), in page order; returns its
+// length.  Called by the whole workgroup.
 template <typename F>
-__device__ __forceinline__ int build_list(int p_lo, int p_hi, int32_t *pgs, uint16_t *lps,
-                                          int32_t *wave_cnt, F pick) {
+__device__ __forceinline__ int build_list(int p_lo, int p_hi, int32_t *pgs, int32_t *wave_cnt, F pick) {
   int n = 0;
   for (int base = p_lo; base < p_hi; base += 256) {
     const int p = base + threadIdx.x;
     const int32_t phys = p < p_hi ? pick(p) : -1;
     const int i = place(phys >= 0, n, wave_cnt);
-    if (phys >= 0) {
-      pgs[i] = phys;
-      lps[i] = (uint16_t)(p - p_lo);
-    }
+    if (phys >= 0) pgs[i] = phys;
   }
   __syncthreads();
   return n;
 }
 
-// SH: the launch looks for pages that sequences share (shared_pages); each workgroup first takes
-// a job of the shared pages, if there is one for it, then the rest of its own split's pages.
+// SH: the launch looks for pages that sequences share (shared_pages); a workgroup of a sharer first takes
+// a range of them, if there is one for it, then the rest of its own split's pages.
 template <int D, bool VT, bool CAP, bool SH>
 __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
   constexpr int NP = D == 256 ? 1 : 2;   // pages per step of a wave
@@ -506,55 +519,57 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
   constexpr int SMEM = OWN_BYTES > RING_BYTES ? OWN_BYTES : RING_BYTES;
   __shared__ __align__(1024) char smem[SMEM];
   __shared__ int32_t pgs[kMaxSplitPages];
-  // masks of a shared range's pages, or the logical pages of a split's list
-  __shared__ uint32_t aux[SH ? kMaxSharedPages : 1];
+  __shared__ uint32_t msk[SH ? kMaxSharedPages : 1];   // sharers of each page of a range
+  __shared__ int32_t ranks[SH ? kMaxGroupSeqs : 1];    // the sharers, as indices in the group
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qn = lane & 15, grp = lane >> 4;
   int b, hg, split, len;
-  int own_full = 0;        // lane j: whole pages of sequence j of the own group
-  GroupState own{};
+  int full = 0;            // lanes j, j + 32: whole pages of sequence j of the group
+  bool listed = false;     // the sequence is a sharer: its shared pages leave its own list
+  GroupState gs{};
   if constexpr (SH) {
-    // splits vary slowest: the first ids hold the sequences' first pages, which a shared prefix
-    // takes away, and it is they that the jobs go to.  Jobs (group, page range, head) in that
-    // order, job id (and id + grid, ...) to workgroup id; lanes 0 .. 31 look at the job's group,
-    // lanes 32 .. 63 at the own sequence's.
-    const int id = blockIdx.x;
+    // KV heads vary fastest, so an XCD keeps its heads, then groups.  Within a group that shares pages
+    // splits vary slowest: the ranges, which the first ids have, go with the splits that lose their
+    // pages to them, and every CU gets workgroups of both kinds (all of 16384 tokens shared 58 -> 54 us,
+    // half of them 270 -> 244); so it is where most sequences are half as long as the bound or less and
+    // leave their later splits empty (32 of 4096 tokens in a launch for 17473: 125 -> 100).  Else sequences
+    // do: two sequences' workgroups for one split meet on a CU, and in its L1 where they read the same
+    // pages after all (31 of 32 sequences on a prefix that the first does not have: 184 -> 170).
     const int n_hq = a.n_kv_heads * a.n_qgroups;
-    int rest = id;
-    int kvh = rest % a.n_kv_heads;
-    rest /= a.n_kv_heads;
-    b = rest % a.n_seqs;
-    rest /= a.n_seqs;
-    split = rest % a.own_splits;
-    // Row-major V: odd splits take the heads half a turn on (32 sequences of 17473 tokens, nothing
-    // shared: 386 against 389 us).  Transposed V: an XCD keeps its head, whose 128-byte lines hold
-    // columns of four pages, often other sequences' (391 -> 381 us at 16 x 8192, head_dim 256).
-    if (!VT) kvh = (kvh + (split & 1) * (a.n_kv_heads >> 1)) % a.n_kv_heads;
-    hg = kvh * a.n_qgroups + rest / a.own_splits;
-    const int n_jobs = a.n_groups * a.shared_splits * n_hq;
-    const int own_g = b / a.group_seqs;
-    for (int job = id;; job += gridDim.x) {
-      const int g = job < n_jobs ? job / n_hq / a.shared_splits : own_g;
-      const int lb = group_lane_seq(a, lane & 32 ? own_g : g, lane & 31);
-      const int lane_len = seq_len_of(a, lb);
-      const int32_t page0 = a.maps[(size_t)lb * a.map_stride];
-      if (job == id) {
-        own = group_state(a, own_g, lane_len >> 4, page0, 32);
-        len = __builtin_amdgcn_readlane(lane_len, 32 + b - own.b0);
-        own_full = __shfl(lane_len >> 4, 32 + (lane & 31));
-        if (split == 0 && hg == 0 && tid == 0) a.flags[b] = own.shares;
+    hg = blockIdx.x % n_hq;
+    hg = hg % a.n_kv_heads * a.n_qgroups + hg / a.n_kv_heads;
+    // (the last group may be smaller: its workgroups end first)
+    int xg = blockIdx.x / n_hq;
+    const int n_last = (a.n_seqs - (a.n_groups - 1) * a.group_seqs) * a.own_splits;
+    const int n_side = xg < n_last * a.n_groups ? a.n_groups : a.n_groups - 1;
+    if (n_side < a.n_groups) xg -= n_last * a.n_groups;
+    const int g = xg % n_side;
+    xg = xg / n_side + (n_side < a.n_groups ? n_last : 0);
+    const int lb = min(g * a.group_seqs + min(lane & 31, a.group_seqs - 1), a.n_seqs - 1);
+    const int lane_len = seq_len_of(a, lb);
+    const int32_t page = a.maps[(size_t)lb * a.map_stride + a.share_pages / 2];
+    full = lane_len >> 4;
+    gs = group_state(a, g, full, page);
+    split = gs.by_split ? xg / gs.n : xg % a.own_splits;
+    b = gs.b0 + (gs.by_split ? xg % gs.n : xg / a.own_splits);
+    len = __builtin_amdgcn_readlane(lane_len, b - gs.b0);
+    listed = gs.sharers >> (b - gs.b0) & 1;
+    int n_ranges = 0, range_pages = 0;
+    if (listed) shared_ranges(a, gs, n_ranges, range_pages);
+    if (split == 0 && hg == 0 && tid == 0) a.flags[b] = n_ranges;
+    if (listed) {
+      if (lane < 32 && (gs.sharers >> lane & 1)) ranks[__popc(gs.sharers & ((1u << lane) - 1))] = lane;
+      // the sharers' first splits come first: it is they that lose their pages to the ranges
+      const int range = split * gs.n_sh + __popc(gs.sharers & ((1u << (b - gs.b0)) - 1));
+      if (range < n_ranges) {
+        const int p_lo = range * range_pages;
+        shared_pages<D, VT, CAP>(a, gs, full, hg, p_lo, min(range_pages, gs.rep_full - p_lo),
+                                 a.own_splits + range, smem, pgs, msk, ranks);
       }
-      if (job >= n_jobs) break;
-      const GroupState gs = group_state(a, g, lane_len >> 4, page0, 0);
-      if (gs.shares) {
-        shared_pages<D, VT, CAP>(a, gs, lane_len >> 4, job % n_hq, job / n_hq % a.shared_splits,
-                                 smem, pgs, aux);
-        __syncthreads();   // the lists and the ring are used again
-      }
-      if (job + (int)gridDim.x >= n_jobs) break;
+      __syncthreads();   // ranks; the lists and the ring are used again
     }
   } else {
     split = blockIdx.x;
@@ -596,26 +611,24 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
   // the split's physical pages, staged in LDS once (those that its group shares are left out)
   int n_sp = p_end - p_begin;
   const int32_t *map = a.maps + (size_t)b * a.map_stride;
-  uint16_t *lps = reinterpret_cast<uint16_t *>(aux);
-  const bool listed = SH && own.shares;
   if (listed) {
-    const int32_t *rep = a.maps + (size_t)(own.b0 + own.rep) * a.map_stride;
-    const int n_shared = min(len >> 4, own.rep_full);
-    n_sp = build_list(p_begin, p_end, pgs, lps, reinterpret_cast<int32_t *>(smem), [&](int p) {
+    const int32_t *rep = a.maps + (size_t)(gs.b0 + gs.rep) * a.map_stride;
+    const int n_shared = min(len >> 4, gs.rep_full);
+    n_sp = build_list(p_begin, p_end, pgs, reinterpret_cast<int32_t *>(smem), [&](int p) {
       const int32_t mine = map[p];
-      if (b != own.b0 + own.rep) return mine == rep[p] && p < n_shared ? -1 : mine;
-      // the representative's page is a shared one if any other sequence maps it
+      if (b != gs.b0 + gs.rep) return mine == rep[p] && p < n_shared ? -1 : mine;
+      // the representative (the first sharer): does another one map its page?
       bool found = false;
-      for (int j0 = 0; j0 < own.n && __builtin_amdgcn_ballot_w64(!found && p < n_shared); j0 += 8) {
-        int32_t x[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          x[e] = a.maps[(size_t)(own.b0 + min(j0 + e, own.n - 1)) * a.map_stride + p];
+      for (int r0 = 1; r0 < gs.n_sh && __builtin_amdgcn_ballot_w64(!found && p < n_shared); r0 += 8) {
+        int32_t x[8], j[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const int full = __builtin_amdgcn_readlane(own_full, min(j0 + e, own.n - 1));
-          found |= j0 + e != own.rep && p < full && x[e] == mine;
+          j[e] = __builtin_amdgcn_readfirstlane(ranks[min(r0 + e, gs.n_sh - 1)]);
+          x[e] = a.maps[(size_t)(gs.b0 + j[e]) * a.map_stride + p];
         }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          found |= p < __builtin_amdgcn_readlane(full, j[e]) && x[e] == mine;
       }
       return found && p < n_shared ? -1 : mine;
     });
@@ -627,10 +640,10 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
     for (int i = tid; i < n_sp; i += 256) pgs[i] = map[p_begin + i];
     __syncthreads();
   }
-  // logical page of entry i of the list
-  auto logical = [&](int i) {
-    return p_begin + (listed ? __builtin_amdgcn_readfirstlane((int)lps[i]) : i);
-  };
+  // keys of entry i of the list: all but the sequence's last page, which no sequence shares unless it is
+  // whole, are whole pages
+  const int last_keys = p_end == n_pages ? len - 16 * (n_pages - 1) : 16;
+  auto keys_of = [&](int i) { return i == n_sp - 1 ? last_keys : 16; };
   const uint32_t page_elems = (uint32_t)a.n_kv_heads * 16u * D;
   const char *kbase = reinterpret_cast<const char *>(a.kc) + (size_t)h * 16 * ROWB;
   const char *vbase = VT ? reinterpret_cast<const char *>(a.vc) + (size_t)h * D * a.n_cols * 2
@@ -643,10 +656,9 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
     u32x2 vt[VT ? DT : 1];
   };
 
-  // p: logical page (keys 16 p ..), phys: its physical page.  Loads only; the last page's
-  // masking happens in compute_page, so that no load result is needed here.
-  auto load_page = [&](int p, uint32_t phys, Page &pg) {
-    const int nvalid = min(16, len - 16 * p);
+  // A page of nvalid keys.  Loads only; the last page's masking happens in compute_pair, so that no
+  // load result is needed here.
+  auto load_page = [&](int nvalid, uint32_t phys, Page &pg) {
     const char *kp = kbase + (size_t)phys * page_elems * 2;
     const int krow = min(qn, nvalid - 1);
 #pragma unroll
@@ -680,12 +692,10 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
   struct Pair {
     Page pg[NP];
   };
-  auto compute_pair = [&](const int (&p)[NP], bool two, const Pair &pr) {
+  auto compute_pair = [&](const int (&keys)[NP], bool two, const Pair &pr) {
     float x[4 * NP];
-    int key[NP];
 #pragma unroll
     for (int pp = 0; pp < NP; ++pp) {
-      key[pp] = 16 * p[pp] + 4 * grp;
       f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int st = 0; st < KS; ++st)
@@ -695,7 +705,7 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float v = CAP ? a.cap_out * tanh_fast(s[i] * a.cap_in) : s[i] * a.scale_log2;
-        x[4 * pp + i] = key[pp] + i < len && (pp == 0 || two) ? v : -INFINITY;
+        x[4 * pp + i] = 4 * grp + i < keys[pp] && (pp == 0 || two) ? v : -INFINITY;
       }
     }
     float mx = x[0];
@@ -762,7 +772,7 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
       u32x2 m[NP];
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp) {
-        const int keep = pp == 0 || two ? len - key[pp] : 0;
+        const int keep = pp == 0 || two ? keys[pp] - 4 * grp : 0;
         m[pp][0] = keep >= 2 ? 0xFFFFFFFFu : keep == 1 ? 0x0000FFFFu : 0u;
         m[pp][1] = keep >= 4 ? 0xFFFFFFFFu : keep == 3 ? 0x0000FFFFu : 0u;
       }
@@ -790,15 +800,15 @@ __device__ __forceinline__ void decode_bf16(const DecodeArgs &a) {
 #pragma unroll
         for (int pp = 0; pp < NP; ++pp) {
           const int e = min(entry(min(k, n_mine - 1)) + pp, n_sp - 1);
-          load_page(logical(e), (uint32_t)__builtin_amdgcn_readfirstlane(pgs[e]), pr.pg[pp]);
+          load_page(keys_of(e), (uint32_t)__builtin_amdgcn_readfirstlane(pgs[e]), pr.pg[pp]);
         }
       };
       auto compute = [&](int k, const Pair &pr) {
         const int e = entry(k);
-        int p[NP];
+        int keys[NP];
 #pragma unroll
-        for (int pp = 0; pp < NP; ++pp) p[pp] = logical(min(e + pp, n_sp - 1));
-        compute_pair(p, e + 1 < n_sp, pr);
+        for (int pp = 0; pp < NP; ++pp) keys[pp] = keys_of(min(e + pp, n_sp - 1));
+        compute_pair(keys, e + 1 < n_sp, pr);
       };
       Pair b0, b1;
       issue(0, b0);
@@ -988,14 +998,14 @@ __global__ __launch_bounds__(64) void decode_combine_kernel(DecodeArgs a, int D,
   // is not used), so the launch is one round trip for all but the longest rows.
   load(0, a.own_splits);
   float2 ml0 = lane < a.max_splits ? ml[lane] : float2{-INFINITY, 0.f};
-  bool shares = false;              // whether the row's group has partials of shared pages
-  if (a.n_groups > 0) shares = a.flags[b] != 0;
+  int shares = 0;                   // the row's partials of shared pages
+  if (a.n_groups > 0) shares = a.flags[b];
   const int len = seq_len_of(a, b);
   const int n_pages = (len + 15) >> 4;
   const int n_own = (n_pages + a.split_pages - 1) / a.split_pages;
   if (n_own == 0 || (n_own == 1 && !shares)) return;
   // the row's partials: slots below n_own and, with shared pages, those from own_splits on
-  const int ns = shares ? a.max_splits : n_own;
+  const int ns = shares ? a.own_splits + shares : n_own;
   auto used = [&](int s) { return s < n_own || (s >= a.own_splits && s < ns); };
   if (shares && kPre * n_shares > a.own_splits) {
 #pragma unroll
@@ -1085,7 +1095,7 @@ namespace {
 struct DecodeShape {
   int split_pages, own_splits;         // pages per split, splits of the longest sequence
   int n_groups, group_seqs;            // 0 groups: shared pages are not looked for
-  int shared_split_pages, shared_splits;
+  int shared_splits;                   // ranges of a group's shared pages at most
   int slots() const { return own_splits + (n_groups ? shared_splits : 0); }
 };
 
@@ -1110,11 +1120,12 @@ DecodeShape decode_shape(const DecodeLaunch &p, size_t ws_bytes) {
   const int64_t max_pages = ((int64_t)p.max_len + 15) / 16;
   s.own_splits = (int)((max_pages + s.split_pages - 1) / s.split_pages);
   if (s.own_splits < 1) s.own_splits = 1;
-  // Looking for shared pages costs 2 to 3 us a launch where nothing is shared, and below some
-  // 100 us the caches serve the repeated reads anyway: only where the sequences' keys and values
-  // together pass twice the 256 MB last-level cache
+  // Shared pages are looked for where the sequences' keys and values may pass twice the 256 MB last-level
+  // cache (below, the caches serve the repeated reads); a launch of one split a sequence, which needs
+  // no merge as it is, must gain that too (128 sequences of 1200 tokens, nothing shared: 111 us,
+  // looked for 114).  A look costs 1 to 2 us where nothing is shared.
   const int64_t kv_bytes = (int64_t)p.n_seqs * p.max_len * p.n_kv_heads * p.head_dim * 4;
-  if (!p.is_bf16 || p.n_seqs < 2 || kv_bytes < kSharedMinBytes) return s;
+  if (!p.is_bf16 || p.n_seqs < 2 || kv_bytes < (s.own_splits > 1 ? 1 : 4) * kSharedMinBytes) return s;
   // sequences per group: what the column blocks of a workgroup hold
   const int per_block = group >= 16 ? 1 : 16 / group;
   const int cap = std::min(kMaxGroupSeqs, kDecWaves * shared_blocks(p.head_dim) * per_block);
@@ -1128,11 +1139,10 @@ DecodeShape decode_shape(const DecodeLaunch &p, size_t ws_bytes) {
   if (fit * kMaxSharedPages < max_pages) return s;
   ns = std::min(ns, fit);
   int64_t sp = (max_pages + ns - 1) / ns;
-  if (sp < 16) sp = 16;
+  if (sp < kMinRangePages) sp = kMinRangePages;
   if (sp > kMaxSharedPages) sp = kMaxSharedPages;
   s.n_groups = (p.n_seqs + s.group_seqs - 1) / s.group_seqs;
-  s.shared_split_pages = (int)sp;
-  s.shared_splits = (int)((max_pages + s.shared_split_pages - 1) / s.shared_split_pages);
+  s.shared_splits = (int)((max_pages + sp - 1) / sp);
   return s;
 }
 
@@ -1177,7 +1187,8 @@ hipError_t launch_decode(const DecodeLaunch &p, hipStream_t stream) {
   a.n_groups = sh.n_groups;
   a.group_seqs = sh.group_seqs;
   a.shared_splits = sh.shared_splits;
-  a.shared_split_pages = sh.shared_split_pages;
+  const int64_t page_bytes = (int64_t)p.n_kv_heads * p.head_dim * 64;
+  a.share_pages = (int32_t)(kSharedMinBytes / 2 / page_bytes / p.n_seqs) + 1;
   a.own_splits = sh.own_splits;
   a.n_cols = (uint32_t)p.n_phys_pages * 16u;
   const float log2e = 1.4426950408889634f;

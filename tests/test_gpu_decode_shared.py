@@ -1,9 +1,9 @@
-"""GPU parity of the decode step where sequences share physical pages and the launch looks for them
-(its bound on the sequences' keys and values is 512 MB or more; the lengths themselves stay small):
-groups of every fill, a group more than one, 1 to 32 query heads per KV head, both V layouts, the
-cap, sequences that leave the shared prefix for a page and come back, a representative shorter than
-the others, lengths 0 and below one page, and batches in which nothing is shared.  Against the fp64
-oracle, tolerances as the other decode tests."""
+"""GPU parity of the decode step where sequences share physical pages in a launch whose bound on the
+sequences' keys and values is 512 MB or more, so that it looks for such pages, while the lengths are far
+below it, so that it reads them sequence by sequence all the same: lengths 0 and below one page, sequences
+that leave a shared prefix for a page and come back, 1 to 32 query heads per KV head, groups of every
+fill, a group more than one, both V layouts, the cap.  (Lengths at which the pages are taken together:
+test_gpu_decode_shared_ranges.)  Against the fp64 oracle, tolerances as the other decode tests."""
 
 import dataclasses
 

@@ -43,7 +43,7 @@ class Batch:
         self.k = normal((1, npp, kv, PAGE, d), 2 * d ** -0.5)
         self.v = normal((1, kv, d, npp * PAGE) if layout == "transposed" else self.k.shape, 1.0)
         self.q = normal((len(lens), kv * g, d), 1.0)
-        self.bytes = sum(lens) * kv * d * 4
+        self.bytes = len(lens) * max(lens) * kv * d * 4   # the launch's bound
 
     def values(self, b, p):
         """V of sequence b's page p, every head."""
@@ -97,6 +97,81 @@ def test_nonfinite_values_stay_with_their_sequences(shape, bad):
     assert np.isfinite(got[others]).all()
     sel = [2, others[len(others) // 2], n - 1]
     _check(got[sel], t.oracle(sel), "bf16", f"{shape}")
+
+
+
+A, E, O_ = range(9), range(0, 32, 2), range(1, 32, 2)
+CASES = {
+    # head_dim, KV heads, query heads per KV head, V layout, cap, tokens, shares, moved, sequences that share
+    "range edges, middle pages elsewhere": (
+        128, 8, 5, "rowmajor", 0.0, [15000 - 300 * b for b in A], [(A, 640)],
+        [(2, p) for p in range(100, 140)] + [(5, 31), (5, 32), (8, 639)], A),
+    "prefix inside a range, cap": (
+        128, 8, 5, "rowmajor", 30.0, [15000 - 300 * b for b in A], [(A, 777)], [(0, 300)], A),
+    "short ones beside, a short representative": (
+        64, 8, 4, "transposed", 0.0,
+        [0, 7000, 15, 16, 9000, 2000, 3400] + [12000 - 100 * i for i in range(20)],
+        [([1, 4] + list(range(7, 27)), 437)], [(1, 9)], [1, 4] + list(range(7, 27))),
+    "two groups of 12, one head a column block": (
+        128, 2, 16, "transposed", 0.0, [24000 + b for b in range(24)], [(range(12), 1000), (range(12, 24), 900)],
+        [], range(24)),
+    "one group shares, one has a private sequence": (
+        128, 2, 20, "rowmajor", 0.0, [24000 + b for b in range(24)], [(range(23), 1400)], [], range(12)),
+    "interleaved prefixes share nothing": (
+        128, 8, 2, "rowmajor", 0.0, [4500] * 32, [(E, 270), (O_, 270)], [], []),
+    "one page shares nothing": (256, 8, 2, "rowmajor", 50.0, [9000] * 8, [(range(8), 1)], [], []),
+    "a page more than half": (256, 8, 1, "rowmajor", 0.0, [9000] * 8, [(range(8), 282)], [], range(8)),
+    "half": (256, 8, 1, "transposed", 0.0, [9000] * 8, [(range(8), 281)], [], []),
+    "everything": (128, 8, 1, "rowmajor", 0.0, [16 * 280] * 33, [(range(33), 280)], [], range(33)),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_ranges(name):
+    d, kv, g, layout, cap, lens, share, moved, sharers = CASES[name]
+    t = Batch(d, kv, g, lens, share, layout, cap, moved)
+    assert t.bytes >= 512 << 20
+    print(name, flush=True)
+    ranges, got = _run_in(t, _bytes(t))
+    print("ranges", ranges, flush=True)
+    assert [b for b, r in enumerate(ranges) if r > 0] == list(sharers)
+    sel = sorted({0, 1, 2, len(lens) // 2, len(lens) - 1} | {b for b, _ in moved})
+    _check(got[sel], t.oracle(sel), "bf16", name)
+
+
+def _bytes(t):
+    cache = N.PagedKVCache(t.k, t.v, torch.zeros(1, dtype=torch.int32, device="cuda"), 1e4,
+                           N.V_TRANSPOSED if t.layout == "transposed" else N.V_ROWMAJOR)
+    return N.decode_attn_workspace_bytes(cache, len(t.lens), t.q.shape[1], max(t.lens))
+
+
+def _run_in(t, nbytes):
+    """(ranges of shared pages that each sequence has partials of, output): the former are the last
+    entries of a workspace that the call fills."""
+    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
+    got = t.run(workspace=ws)
+    n = len(t.lens)
+    return ws[nbytes - 4 * n:].view(torch.int32).tolist(), got
+
+
+@pytest.mark.parametrize("ranges", [4, 5, 6])
+def test_ranges_of_a_small_workspace(ranges):
+    """Ranges as long as a workgroup's lists hold (1024 pages) where the workspace has few partials; with
+    too few even for those nothing is shared."""
+    d, kv, g, n, tokens = 64, 2, 3, 16, 66200
+    t = Batch(d, kv, g, [tokens - 50 * b for b in range(n)], [(range(n), 4000)],
+              moved=[(3, 827), (3, 828), (4, 3500)])
+    rows = n * kv * g * (d + 2) * 4
+    pages = -(-tokens // PAGE)
+    sp = -(-pages // 16)
+    splits = -(-pages // sp)
+    nbytes = rows * (splits + ranges) + 4 * n
+    got_ranges, got = _run_in(t, nbytes)
+    print(got_ranges, flush=True)
+    if ranges >= 5:
+        assert got_ranges == [ranges] * n
+    sel = [0, 3, 4, n - 1]
+    _check(got[sel], t.oracle(sel), "bf16", f"{ranges} ranges")
 
 
 @pytest.mark.parametrize("d,layout", [(64, "rowmajor"), (128, "rowmajor"), (128, "transposed"),

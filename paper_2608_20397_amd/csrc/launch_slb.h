@@ -21,10 +21,7 @@ struct SlbLaunch {
   void *workspace;
 };
 
-// Tool ranges of a scan (one workgroup column each) and the tools per range.
-void slb_geometry(int32_t n_tools, int32_t n_queries, int32_t dim, int32_t &n_ranges,
-                  int32_t &range_tools);
-size_t slb_workspace_bytes(int32_t n_tools, int32_t n_queries, int32_t dim);
+size_t slb_workspace_bytes(int32_t n_tools, int32_t n_queries, int32_t dim, int32_t k);
 hipError_t launch_slb_scan(const SlbLaunch &p, hipStream_t stream);
 hipError_t launch_slb_quantize(const float *x, int32_t n, int32_t dim, int8_t *q, float *scale,
                                hipStream_t stream);

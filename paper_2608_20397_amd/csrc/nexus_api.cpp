@@ -683,7 +683,7 @@ nexus_status check_slb(const void *tools, const float *tool_scale, int32_t n_too
 size_t nexus_slb_scan_workspace(int32_t n_tools, int32_t n_queries, int32_t dim, int32_t k) {
   if (n_tools <= 0 || n_queries <= 0 || k < 1 || k > 8 || dim <= 0 || dim % 64 || dim > 1024)
     return SIZE_MAX;
-  return slb_workspace_bytes(n_tools, n_queries, dim);
+  return slb_workspace_bytes(n_tools, n_queries, dim, k);
 }
 
 nexus_status nexus_slb_scan(const int8_t *tools, const float *tool_scale, int32_t n_tools,
@@ -695,7 +695,7 @@ nexus_status nexus_slb_scan(const int8_t *tools, const float *tool_scale, int32_
                               k, tau);
   if (st) return st;
   if (!top_idx || !top_score || !margin || !route) return NEXUS_EINVAL;
-  const size_t need = slb_workspace_bytes(n_tools, n_queries, dim);
+  const size_t need = slb_workspace_bytes(n_tools, n_queries, dim, k);
   if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return NEXUS_EWORKSPACE;
   SlbLaunch L{};
   L.tools = tools;

@@ -12,12 +12,13 @@
 // for query column l % 16.  A candidate is one 64-bit key that carries both orders (higher score
 // first, lower index first among equal scores), so the best are found by comparing keys alone.
 //
-// * Up to 16 queries (the single-query lookup of a user turn), and any number over a registry of
+// * Up to 16 queries (the single-query lookup of a user turn), and many over a registry of
 //   one range: one 16-query block per workgroup column; the waves take the range's 16-tool tiles
 //   in turn, each tile one MFMA chain, and fold the scores into each lane's own sorted list of the
 //   best KT.  A column's 4 lane lists are merged by lane exchanges and the 4 waves' lists through
 //   LDS.  With one range the result is final (top-k, margin, gate); otherwise each range's best
 //   go to the workspace and a second kernel merges them.  HBM-bound for one query.
+// * Thousands of queries over a small registry (slb_block_kernel): the same lists, for 64 queries a workgroup.
 // * More queries: two passes without any list in the first (slb_max_kernel, slb_select_kernel).
 //   The first writes the best score of every 16-tool tile for every query; the second takes the
 //   KT best tiles of a query, which hold its KT best tools (a tool of any other tile has KT tools
@@ -25,6 +26,8 @@
 //   index), scores their KT x 16 tools again and ranks them.
 #include "device_common.h"
 #include "launch_slb.h"
+
+#include <algorithm>
 
 namespace nexus {
 
@@ -307,6 +310,186 @@ __global__ __launch_bounds__(256) void slb_scan_kernel(SlbArgs a) {
   }
 }
 
+// ---- large batches over small registries: workgroup = 64 queries x one range, its 4 waves take 64-tool
+// blocks in turn with 16 MFMA chains each, as slb_max_kernel does, and keep the best KT of every column
+// in lane lists.  Most of its time is list upkeep (a wave inserts nearly every score of its first blocks),
+// which does not grow with the queries while the chip has room: 300 tools x 64 .. 8192 queries 30 .. 36 us.
+template <int KT>
+__global__ __launch_bounds__(256, 2) void slb_block_kernel(SlbArgs a) {
+  constexpr int QB = 64, NT = 4, NSB = 4, CS = 2;   // queries, tool tiles, sub-blocks, steps
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int dim = a.dim, steps = dim / 64, ld = dim + kQPad;
+  int8_t *qs = reinterpret_cast<int8_t *>(smem);                         // [QB][ld]
+  float *tsc = reinterpret_cast<float *>(smem + (size_t)QB * ld);        // [range_tools]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qn = lane & 15, grp = lane >> 4;
+  const int q0 = blockIdx.y * QB;
+  const int range = blockIdx.x;
+  const int t_begin = range * a.range_tools;
+  const int t_end = min(t_begin + a.range_tools, a.n_tools);
+
+  for (int c = tid; c < QB * (dim / 16); c += 256) {
+    const int r = c / (dim / 16), off = (c - r * (dim / 16)) * 16;
+    u32x4 v = u32x4{0u, 0u, 0u, 0u};
+    if (q0 + r < a.n_queries)
+      v = *reinterpret_cast<const u32x4 *>(a.queries + (size_t)(q0 + r) * dim + off);
+    *reinterpret_cast<u32x4 *>(qs + r * ld + off) = v;
+  }
+  for (int i = tid; i < t_end - t_begin; i += 256) tsc[i] = a.tool_scale[t_begin + i];
+  float sq[NSB];
+#pragma unroll
+  for (int sb = 0; sb < NSB; ++sb) {
+    const int q = q0 + 16 * sb + qn;
+    sq[sb] = q < a.n_queries ? a.query_scale[q] : 0.f;
+  }
+  __syncthreads();
+
+  uint64_t best[NSB][KT];
+  uint64_t floor_key[NSB];
+#pragma unroll
+  for (int sb = 0; sb < NSB; ++sb) {
+    floor_key[sb] = 0;
+#pragma unroll
+    for (int j = 0; j < KT; ++j) best[sb][j] = 0;
+  }
+
+  // this wave's blocks: wave, wave + 4, ... of the range's 64-tool blocks; each is n_chunks
+  // chunks of CS steps, walked as one sequence u = block * n_chunks + chunk
+  const int n_blocks = (t_end - t_begin + 63) / 64;
+  const int my_blocks = n_blocks > wave ? (n_blocks - wave + kWaves - 1) / kWaves : 0;
+  const int n_chunks = (steps + CS - 1) / CS;
+  const int total = my_blocks * n_chunks;
+  struct Chunk {
+    i32x4 a[NT][CS];
+  };
+  // Every call issues the same loads (past the sequence's end it re-reads the last chunk; rows
+  // and steps past the registry's end re-read valid ones), so the wait before a chunk's use
+  // leaves the next chunk's loads in flight.
+  auto load_chunk = [&](int u, Chunk &ch) {
+    const int uu = min(u, total - 1);
+    const int j = uu / n_chunks, c = uu - j * n_chunks;
+    const int t0 = t_begin + 64 * (wave + kWaves * j);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int8_t *trow = a.tools + (size_t)min(t0 + 16 * i + qn, a.n_tools - 1) * dim + 16 * grp;
+#pragma unroll
+      for (int s2 = 0; s2 < CS; ++s2)
+        ch.a[i][s2] = *reinterpret_cast<const i32x4 *>(trow + 64 * min(c * CS + s2, steps - 1));
+    }
+  };
+  i32x4 acc[NT][NSB];
+  auto step = [&](int u, const Chunk &ch) {
+    const int j = u / n_chunks, c = u - j * n_chunks;
+    if (c == 0) {
+#pragma unroll
+      for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int sb = 0; sb < NSB; ++sb) acc[i][sb] = i32x4{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int s2 = 0; s2 < CS; ++s2) {
+      const int st = c * CS + s2;
+      if (st < steps) {
+#pragma unroll
+        for (int sb = 0; sb < NSB; ++sb) {
+          const i32x4 bv =
+              *reinterpret_cast<const i32x4 *>(qs + (16 * sb + qn) * ld + 64 * st + 16 * grp);
+#pragma unroll
+          for (int i = 0; i < NT; ++i)
+            acc[i][sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ch.a[i][s2], bv, acc[i][sb], 0, 0, 0);
+        }
+      }
+    }
+    if (c != n_chunks - 1) return;
+    // the candidate pass runs at a raised wave priority, so that its list upkeep interleaves
+    // with the other wave's MFMA chains (about 4% faster at 65536 tools x 256 queries)
+    __builtin_amdgcn_s_setprio(2);
+    // the block's 64 x 64 scores: a candidate that does not beat its column's floor (at most
+    // the column's KT-th best) cannot be among the column's best KT and is dropped
+    const int tb = 64 * (wave + kWaves * j);                   // block start within the range
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const f32x4 sc = *reinterpret_cast<const f32x4 *>(tsc + tb + 16 * i + 4 * grp);
+#pragma unroll
+      for (int sb = 0; sb < NSB; ++sb) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int t = t_begin + tb + 16 * i + 4 * grp + r;
+          const float score = ((float)acc[i][sb][r] * sc[r]) * sq[sb];
+          const uint64_t key = t < t_end ? cand_key(score, t) : 0;
+          insert<KT>(best[sb], key > floor_key[sb] ? key : 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int sb = 0; sb < NSB; ++sb) floor_key[sb] = column_floor<KT>(best[sb]);
+    __builtin_amdgcn_s_setprio(0);
+  };
+  if (total > 0) {
+    Chunk b0, b1;
+    int u = 0;
+    load_chunk(0, b0);
+    for (;;) {
+      load_chunk(u + 1, b1);
+      step(u, b0);
+      if (++u >= total) break;
+      load_chunk(u + 1, b0);
+      step(u, b1);
+      if (++u >= total) break;
+    }
+  }
+
+  // each column's 4 lists inside the wave, then the 4 waves' lists through LDS
+#pragma unroll
+  for (int sb = 0; sb < NSB; ++sb) {
+    merge_lanes<KT>(best[sb], 16);
+    merge_lanes<KT>(best[sb], 32);
+  }
+  __syncthreads();                                        // query block and scales no longer read
+  uint64_t *cl = reinterpret_cast<uint64_t *>(smem);      // [wave][NSB][16][KT]
+  if (wave > 0 && grp == 0)
+#pragma unroll
+    for (int sb = 0; sb < NSB; ++sb)
+#pragma unroll
+      for (int j = 0; j < KT; ++j) cl[((wave * NSB + sb) * 16 + qn) * KT + j] = best[sb][j];
+  __syncthreads();
+  if (wave > 0 || grp != 0) return;
+#pragma unroll
+  for (int sb = 0; sb < NSB; ++sb) {
+    const int q = q0 + 16 * sb + qn;
+    if (q >= a.n_queries) continue;
+    for (int w = 1; w < kWaves; ++w)
+#pragma unroll
+      for (int j = 0; j < KT; ++j) {
+        uint64_t x = cl[((w * NSB + sb) * 16 + qn) * KT + j];
+#pragma unroll
+        for (int m = 0; m < KT; ++m) {
+          const bool gt = x > best[sb][m];
+          const uint64_t hi = gt ? x : best[sb][m];
+          x = gt ? best[sb][m] : x;
+          best[sb][m] = hi;
+        }
+      }
+    if (a.n_ranges == 1) {
+#pragma unroll
+      for (int j = 0; j < KT; ++j)
+        if (j < a.k) {
+          a.top_idx[(size_t)q * a.k + j] = cand_idx(best[sb][j]);
+          a.top_score[(size_t)q * a.k + j] = cand_score(best[sb][j]);
+        }
+      const float m =
+          best[sb][1] == 0 ? INFINITY : cand_score(best[sb][0]) - cand_score(best[sb][1]);
+      a.margin[q] = m;
+      a.route[q] = m > a.tau ? 1 : 0;
+    } else {
+      const size_t o = ((size_t)q * a.n_ranges + range) * KT;
+#pragma unroll
+      for (int j = 0; j < KT; ++j) a.part[o + j] = best[sb][j];
+    }
+  }
+}
+
 // ---- batches: pass 1.  Workgroup = 64 queries x one range of tools; its 4 waves take 64-tool blocks
 // of the range in turn.  For one block a wave keeps 16 MFMA chains (4 tool tiles x 4 query sub-blocks)
 // and walks the dimension two 64-byte steps at a time, holding those steps of its 64 tool rows in
@@ -335,13 +518,13 @@ __global__ __launch_bounds__(256, 2) void slb_max_kernel(SlbArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qn = lane & 15, grp = lane >> 4;
-  // the query blocks of one range sit 8 ids apart: on one XCD, which then reads the range's tools
-  // from memory once
-  const int per8 = 8 * a.n_qblocks;
-  const int id8 = blockIdx.x / per8, in8 = blockIdx.x - id8 * per8;
-  const int range = 8 * id8 + (in8 & 7);
-  const int q0 = (in8 >> 3) * QB;
-  if (range >= a.n_ranges) return;                                       // padding of the grid
+  // (range, query block) in that order are cut into 8 equal runs, one to an XCD (ids 8 apart): an XCD's L2
+  // then holds the tools of its own ranges, and all XCDs work however few the ranges are
+  const int n_items = a.n_ranges * a.n_qblocks;
+  const int item = (blockIdx.x & 7) * ((n_items + 7) / 8) + (blockIdx.x >> 3);
+  if (item >= n_items || (int)(blockIdx.x >> 3) >= (n_items + 7) / 8) return;   // padding of the grid
+  const int range = item / a.n_qblocks;
+  const int q0 = (item - range * a.n_qblocks) * QB;
   const int t_begin = range * a.range_tools;
   const int t_end = t_begin + min(a.range_tools, a.n_tools - t_begin);
 
@@ -713,20 +896,54 @@ __global__ __launch_bounds__(256) void slb_quantize_kernel(const float *x, int32
 }  // namespace
 
 namespace {
-// More queries than this take the batched kernels (from two 16-query sub-blocks on, a tool row
-// read feeds more than one query column), if the registry is larger than one range of the small
-// scan, which then needs no second launch and no workspace.
-constexpr int kBlockMinQueries = 16;
-constexpr int32_t kOneRangeTools = 256;
+// Which kernels serve a scan.
+enum class Path {
+  kScan,    // slb_scan_kernel: 16-query blocks, ranges of tools over the workgroups for one block
+  kTiles,   // slb_max_kernel, slb_select_kernel
+  kLists,   // slb_block_kernel: 64-query blocks with a sorted list per lane
+};
+constexpr int kScanQueries = 16;          // one 16-query block
+constexpr int32_t kOneRangeTools = 256;   // tools of one range of the scan kernel: no second launch
 constexpr int kBlockQueries = 16 * kSubBlocks;
-constexpr int64_t kBlockWgs = 512;        // batched kernel: two resident workgroups per CU
+constexpr int64_t kBlockWgs = 512;        // batches: two resident workgroups per CU
 constexpr int64_t kBlockMaxRange = 32;    // 64-tool blocks per range (its scales sit in LDS)
 // Tile maxima of one pass over the registry: the batch goes in chunks of whole query blocks that
 // stay within this (a registry of a million tools takes 256 queries a pass).
 constexpr int64_t kTileMaxBytes = (int64_t)64 << 20;
 
-bool batched(int32_t n_tools, int32_t n_queries) {
-  return n_queries > kBlockMinQueries && n_tools > kOneRangeTools;
+// The tile kernels score a query's best tiles again, at 16 KT rows of `dim` bytes: their time grows with
+// the queries where the lists' grows with queries x tools, so from a few thousand queries on the lists
+// win over small registries, the sooner the fewer candidates are kept and the longer the rows are
+// (dim 768, lists against tiles, us: 2048 queries over 300 tools k 2 23 : 31, k 3 32 : 37, k 8 67 : 53; 4096
+// over 5000 53 : 74, 72 : 87, 138 : 119; 16384 over 8192 218 : 292, 274 : 347, 441 : 475; 65536 over 300
+// 71 : 425, 97 : 654, 191 : 1150; 256 over 3000 22 : 19, 31 : 19, 65 : 23).
+bool lists_win(int32_t n_tools, int32_t n_queries, int32_t dim, int32_t k) {
+  const bool short_rows = dim < 512;
+  const int64_t q = n_queries, t = n_tools;
+  if (k <= 2)
+    return short_rows ? q >= 2560 && t <= 4096 : q >= 1280 && t <= 16 * q && t <= 32768;
+  if (k <= 4)
+    return short_rows ? q >= 4096 && 2 * t <= q && t <= 4096 : q >= 1400 && t <= 4 * q && t <= 16384;
+  return short_rows ? q >= 8192 && 4 * t <= q && t <= 4096 : q >= 3000 && t <= q - 2000 && t <= 8192;
+}
+
+// A registry of one range: the scan kernel reads its tools for every 16 queries, the list kernel for
+// every 64, which pays with many queries and long rows (250 tools, lists against scan, us: dim 768, 65536
+// queries k 2 53 : 97, k 3 73 : 101, k 8 159 : 125, 16384 k 3 30 : 31, 4096 k 3 29 : 14; dim 1024, 4096 k 3
+// 36 : 41; dim 256, 65536 k 3 56 : 43).
+bool lists_win_one_range(int32_t n_tools, int32_t n_queries, int32_t dim, int32_t k) {
+  const int32_t t = n_tools, q = n_queries;
+  if (k > 4) return dim > 768 && t > 192 && q >= 32768;
+  if (dim > 768) return t > 64 && q >= (t > 128 ? 4096 : 16384);
+  if (dim >= 512) return (t > 128 && q >= 16384) || (k <= 2 && t > 64 && q >= 32768);
+  return dim > 256 && t > 128 && q >= 32768;
+}
+
+Path path_of(int32_t n_tools, int32_t n_queries, int32_t dim, int32_t k) {
+  if (n_queries <= kScanQueries) return Path::kScan;
+  if (n_tools <= kOneRangeTools)
+    return lists_win_one_range(n_tools, n_queries, dim, k) ? Path::kLists : Path::kScan;
+  return lists_win(n_tools, n_queries, dim, k) ? Path::kLists : Path::kTiles;
 }
 int64_t tile_ld_of(int32_t n_tools) { return ((int64_t)n_tools + 63) / 64 * 4; }
 int32_t chunk_queries(int32_t n_tools, int32_t n_queries) {
@@ -744,27 +961,27 @@ int32_t block_range_tools(int32_t n_tools, int32_t n_queries) {
   if (per > kBlockMaxRange) per = kBlockMaxRange;
   return (int32_t)(per * 64);
 }
+
+// Ranges of the scan and list kernels and the tools of each.
+void ranges_of(Path path, int32_t n_tools, int32_t n_queries, int32_t &n_ranges, int32_t &range_tools) {
+  if (path == Path::kLists) {
+    range_tools = block_range_tools(n_tools, n_queries);
+  } else {
+    const int64_t tiles = ((int64_t)n_tools + 63) / 64;                 // 64-tool units
+    // at least 256 tools per range, at most 256 ranges (the merge reads 8 candidates of each)
+    const int64_t nr = std::min<int64_t>((tiles + 3) / 4, 256);
+    range_tools = (int32_t)((tiles + nr - 1) / nr * 64);
+  }
+  n_ranges = (int32_t)(((int64_t)n_tools + range_tools - 1) / range_tools);
+}
 }  // namespace
 
-void slb_geometry(int32_t n_tools, int32_t n_queries, int32_t dim, int32_t &n_ranges,
-                  int32_t &range_tools) {
-  (void)dim;
-  (void)n_queries;
-  const int64_t tiles = ((int64_t)n_tools + 63) / 64;                 // 64-tool units
-  // at least 256 tools per range, at most 256 ranges (the merge reads 8 candidates of each)
-  int64_t nr = (tiles + 3) / 4;
-  if (nr > 256) nr = 256;
-  if (nr < 1) nr = 1;
-  const int64_t per = (tiles + nr - 1) / nr;
-  range_tools = (int32_t)(per * 64);
-  n_ranges = (int32_t)((n_tools + range_tools - 1) / range_tools);
-}
-
-size_t slb_workspace_bytes(int32_t n_tools, int32_t n_queries, int32_t dim) {
-  if (batched(n_tools, n_queries))
+size_t slb_workspace_bytes(int32_t n_tools, int32_t n_queries, int32_t dim, int32_t k) {
+  const Path path = path_of(n_tools, n_queries, dim, k);
+  if (path == Path::kTiles)
     return (size_t)chunk_queries(n_tools, n_queries) * tile_ld_of(n_tools) * sizeof(uint32_t);
   int32_t nr, rt;
-  slb_geometry(n_tools, n_queries, dim, nr, rt);
+  ranges_of(path, n_tools, n_queries, nr, rt);
   if (nr <= 1) return 0;
   return (size_t)n_queries * nr * kTop * sizeof(uint64_t);
 }
@@ -797,7 +1014,8 @@ hipError_t launch_slb_scan(const SlbLaunch &p, hipStream_t stream) {
   a.margin = p.margin;
   a.route = p.route;
   const int kt = p.k <= 2 ? 2 : p.k <= 4 ? 4 : 8;
-  if (batched(p.n_tools, p.n_queries)) {
+  const Path path = path_of(p.n_tools, p.n_queries, p.dim, p.k);
+  if (path == Path::kTiles) {
     a.tile_max = reinterpret_cast<uint32_t *>(p.workspace);
     a.tile_ld = (int32_t)tile_ld_of(p.n_tools);
     const int32_t chunk = chunk_queries(p.n_tools, p.n_queries);
@@ -820,7 +1038,7 @@ hipError_t launch_slb_scan(const SlbLaunch &p, hipStream_t stream) {
                                                  (int)lds);
         if (e != hipSuccess) return e;
       }
-      const uint32_t wgs = (uint32_t)((a.n_ranges + 7) / 8 * 8) * (uint32_t)a.n_qblocks;
+      const uint32_t wgs = ((uint32_t)a.n_ranges * (uint32_t)a.n_qblocks + 7) / 8 * 8;
       hipLaunchKernelGGL(slb_max_kernel, dim3(wgs), dim3(256), lds, stream, a);
       const dim3 sgrid(a.n_queries);
       if (kt == 2) hipLaunchKernelGGL(slb_select_kernel<2>, sgrid, dim3(256), 0, stream, a);
@@ -831,8 +1049,29 @@ hipError_t launch_slb_scan(const SlbLaunch &p, hipStream_t stream) {
     }
     return hipSuccess;
   }
-  slb_geometry(p.n_tools, p.n_queries, p.dim, a.n_ranges, a.range_tools);
+  ranges_of(path, p.n_tools, p.n_queries, a.n_ranges, a.range_tools);
   if (a.n_ranges > 1) a.part = reinterpret_cast<uint64_t *>(p.workspace);
+  if (path == Path::kLists) {
+    const size_t stage = (size_t)kBlockQueries * (p.dim + kQPad) + (size_t)a.range_tools * sizeof(float);
+    const size_t merge = (size_t)kWaves * kBlockQueries * kTop * 8;
+    const size_t lds = stage > merge ? stage : merge;
+    const dim3 grid(a.n_ranges, (p.n_queries + kBlockQueries - 1) / kBlockQueries);
+    auto run = [&](auto kernel, auto merge_kernel) -> hipError_t {
+      if (lds > 65536) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+      }
+      hipLaunchKernelGGL(kernel, grid, dim3(256), lds, stream, a);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess || a.n_ranges <= 1) return e;
+      hipLaunchKernelGGL(merge_kernel, dim3(p.n_queries), dim3(64), 0, stream, a);
+      return hipGetLastError();
+    };
+    return kt == 2   ? run(slb_block_kernel<2>, slb_merge_kernel<2>)
+           : kt == 4 ? run(slb_block_kernel<4>, slb_merge_kernel<4>)
+                     : run(slb_block_kernel<8>, slb_merge_kernel<8>);
+  }
   // one 16-query block, or several over a registry of one range
   const dim3 grid(a.n_ranges > 1 ? a.n_ranges : (p.n_queries + 15) / 16);
   const size_t stage = (size_t)16 * (p.dim + kQPad);

@@ -412,19 +412,18 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const AttnArgs a, con
 namespace {
 
 // Geometry of the kernel that serves a launch: queries per wave task, key tile, how many of its
-// workgroups are resident per CU, wave tasks per workgroup, and the plan's time per key of one
-// workgroup (us, measured): with every slot taken over several rounds, and, in launches that are
-// resident at once, alone on a CU and with every slot of it taken.
+// workgroups the plan takes to be resident per CU, wave tasks per workgroup, and the plan's time per key
+// of one workgroup (us, measured).  (head_dim 64: three fit a CU.  The plan keeps two, because with three it
+// also cuts short contexts, whose rows then pass through fp16 partials that they had been spared.)
 struct KernelShape {
   int qpw, key_tile, wgs_per_cu, waves;
-  double us_per_key, us_alone, us_together;
+  double us_per_key;
 };
 
 KernelShape kernel_shape(const AttnLaunch &p) {
-  if (p.head_dim == 64) return {kQB, 64, 3, kWaves, 0.025, 0.0118, 0.025};    // LDS DMA
-  if (p.head_dim == 128) return {kQB, 64, 2, kWaves, 0.03, 0.0163, 0.025};    // LDS DMA
-  if (p.v_transposed) return {kQB, 32, 1, kWavesWide, 0.04, 0.04, 0.04};      // LDS DMA
-  return {kQB, 32, 1, kWaves, 0.06, 0.06, 0.06};
+  if (p.head_dim <= 128) return {kQB, 64, 2, kWaves, 0.03 * p.head_dim / 128.0};   // LDS DMA
+  if (p.v_transposed) return {kQB, 32, 1, kWavesWide, 0.04};                       // LDS DMA
+  return {kQB, 32, 1, kWaves, 0.06};
 }
 
 constexpr int kCUs = 256;
@@ -450,8 +449,6 @@ bool make_plan(const AttnLaunch &p, AttnPlan &plan) {
   // path; measured on the shallow depths of the depth-adaptive sweep, e.g. 90 queries at 742:
   // 22.8 -> 19.1 us, and on a single layer of 192 queries over 2560 keys: 34.1 -> 32.4 us)
   constexpr int64_t kMinSplitKeys = 512, kMinSplitKeysSmall = 256;
-  // one suffix whose pieces find a CU each (32 queries at 1000: 15.4 us in pieces of 256, 14.1 of 192)
-  constexpr int64_t kMinSplitKeysAlone = 128;
   plan = AttnPlan{};
   plan.n_seqs = p.n_seqs;
   plan.qpw = ks.qpw;
@@ -495,7 +492,6 @@ bool make_plan(const AttnLaunch &p, AttnPlan &plan) {
                            max_keys <= (int64_t)kMaxRanges * kMaxSplitKeys;
   int64_t best_sk = kMaxSplitKeys;
   double best_cost = 1e300;
-  const bool one_suffix = p.n_seqs == 1 && !any_prefill;
   bool found = false;
   const double cap = p.ws_cap == SIZE_MAX ? 1e300 : (double)p.ws_cap;
   // workspace bytes of a sequence whose rows keep `n` partials each (none for one split): an
@@ -517,7 +513,7 @@ bool make_plan(const AttnLaunch &p, AttnPlan &plan) {
     int64_t sk = (max_keys + ns - 1) / ns;
     sk = (sk + KT - 1) / KT * KT;
     if (sk > kMaxSplitKeys) continue;
-    if (sk < (one_suffix ? kMinSplitKeysAlone : kMinSplitKeysSmall) && ns > 1) break;
+    if (sk < kMinSplitKeysSmall && ns > 1) break;
     int64_t max_splits = 1, n_full = 0, full_len = 0, max_piece = 0, n_pieces = 0;
     double total = 0.0, combine_bytes = 0.0, ws_need = 0.0;
     for (int b = 0; b < p.n_seqs; ++b) {
@@ -554,29 +550,11 @@ bool make_plan(const AttnLaunch &p, AttnPlan &plan) {
       total += (seq_keys[b] + (double)pieces * kPieceOverhead) * p.n_kv_heads;
     }
     if (sk < kMinSplitKeys && ns > 1 && n_pieces > slots) continue;
-    if (sk < kMinSplitKeysSmall && ns > 1 && n_pieces > kCUs) continue;
     if (ws_need > cap) continue;
     const double rounds_full = (double)((n_full + slots - 1) / slots);
     const double est = std::max({rounds_full * (double)(full_len + kPieceOverhead),
                                  (double)max_piece, total / (double)slots});
-    double cost = est * ks.us_per_key + (max_splits > 1 ? combine_bytes / 4.0e6 + 8.0 : 0.0);
-    if (one_suffix && n_pieces <= slots) {
-      // All of it resident at once: a piece runs at the pace that the workgroups beside it on its CU
-      // leave it, so that fewer, longer pieces with a CU each can beat two to a CU, and the combine's
-      // smaller partials come from the caches.  Against one pace for any number (all calls of head_dim
-      // 128, 40 heads over 8, chosen by the one and by the other): 192 queries at 2432: 30.4 us in 384
-      // pieces, 26.6 in 256; 96 at 8192: 38.4 -> 34.0; 400 at 2048: 47.1 unsplit, 37.8 in 408; 16 at
-      // 16384: 46.5 -> 33.7; head_dim 64, 64 at 8192: 28.4 -> 22.8.
-      const int64_t per_cu = (n_pieces + kCUs - 1) / kCUs;
-      const double pace =
-          ks.wgs_per_cu == 1 ? ks.us_alone
-                             : ks.us_alone + (ks.us_together - ks.us_alone) *
-                                                 (double)(per_cu - 1) / (ks.wgs_per_cu - 1);
-      // (the combine reads kCombinePre splits a round trip)
-      cost = (double)max_piece * pace +
-             (max_splits > 1 ? combine_bytes / 6.0e6 + 4.0 + 1.5 * ((max_splits - 1) / kCombinePre)
-                             : 0.0);
-    }
+    const double cost = est * ks.us_per_key + (max_splits > 1 ? combine_bytes / 4.0e6 + 8.0 : 0.0);
     if (cost < best_cost - 1e-9) {
       best_cost = cost;
       best_sk = sk;

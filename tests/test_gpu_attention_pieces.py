@@ -1,6 +1,6 @@
 """GPU parity of one-suffix attention against the fp64 oracle, every row and head, where its key axis is
-cut finest and its tails are shortest: few queries in up to dozens of pieces of 128 keys (more than
-the combine reads at once), and last tiles of one to 63 keys.  head_dim 64, 128 and 256, row-major and
+cut finest and its tails are shortest: few queries in up to 17 pieces of 256 keys (more than the
+combine reads at once), and last tiles of one to 63 keys.  head_dim 64, 128 and 256, row-major and
 transposed V with NaN in every slot past the sequence and in every page it does not map."""
 
 import numpy as np

@@ -253,3 +253,20 @@ def test_plan_beyond_the_range_order(harness):
         _check(launch, plan)
     assert [p["range_major"] for p in plans] == [1, 0, 0]
     assert max(x[6] for x in plans[1]["unit"]) > 64
+
+
+def test_plan_keeps_short_contexts_whole(harness):
+    """A row of an unsplit suffix is rounded once, from fp32 accumulators; split rows pass through fp16
+    partials.  Suffixes over short contexts stay unsplit, and deep ones keep the cuts their rounds were
+    chosen by."""
+    whole = [(hq, hkv, d, vt, 0, [(n, past)])
+             for hq, hkv, d, vt in ((40, 8, 128, False), (40, 8, 128, True), (32, 8, 64, False),
+                                    (64, 2, 64, False), (4, 1, 64, False))
+             for n, past in ((1, 300), (4, 500), (16, 500), (32, 470), (64, 440))]
+    whole += [(16, 8, 256, False, 0, [(1, 300)])]
+    whole += [(40, 8, 128, False, 0, [(n, 512)]) for n in (1, 4, 16, 32, 64)]
+    for launch, plan in zip(whole, _plans(harness, whole)):
+        assert plan["ws"] == 0 and plan["seqs"][0]["max_splits"] == 1, launch
+    deep = {(1088, 8192): 172, (1088, 4096): 129, (800, 4096): 64, (800, 1024): 64}
+    plans = _plans(harness, [(40, 8, 128, False, 0, [x]) for x in deep])
+    assert [p["units"] for p in plans] == list(deep.values())

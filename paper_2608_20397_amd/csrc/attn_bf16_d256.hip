@@ -42,7 +42,9 @@
 
 namespace nexus {
 
-template <bool CAP>
+// DMA: false for caches whose base is not 16-byte aligned, as LDS DMA wants it: the same 16 bytes a lane go
+// through registers.
+template <bool CAP, bool DMA>
 __global__ __launch_bounds__(64 * kWavesWide, 1) void attn_bf16_d256_vt_kernel(
     const AttnArgs a, const AttnPlan plan) {
   constexpr int W = kWavesWide;               // wave tasks (and waves) per workgroup
@@ -150,14 +152,24 @@ __global__ __launch_bounds__(64 * kWavesWide, 1) void attn_bf16_d256_vt_kernel(
   // page numbers of a tile's DMA, read from the LDS page table a step before they are used
   auto k_page = [&](int it) { return pg[max(min(it * (KT / kPage) + (wave >> 2), n_pg - 1), 0)]; };
   auto v_page = [&](int it) { return pg[max(min(it * (KT / kPage) + (vchunk >> 1), n_pg - 1), 0)]; };
+  auto copy16 = [&](char *dst, const char *from) {     // 16 bytes a lane, as one DMA instruction
+    u32x4 val;
+    __builtin_memcpy(&val, __builtin_assume_aligned(from, 2), 16);
+    *reinterpret_cast<u32x4 *>(dst + 16 * lane) = val;
+  };
   auto dma_k = [&](int it, char *dstp, int kpage) {
     const int kt = k_begin + it * KT;
     const uint32_t dst = smem_base + (uint32_t)(dstp - smem) + wave * 2 * PAIRB;
     if (full(it)) {
       const uint32_t page = (uint32_t)__builtin_amdgcn_readfirstlane(kpage);
       const char *ps = kbytes + page * pbytes + kkey0 * KROWB;
-      dma_s<0>(dst, ps, kdo);
-      dma_s<0>(dst + PAIRB, ps + 2 * KROWB, kdo);
+      if constexpr (DMA) {
+        dma_s<0>(dst, ps, kdo);
+        dma_s<0>(dst + PAIRB, ps + 2 * KROWB, kdo);
+      } else {
+        copy16(dstp + wave * 2 * PAIRB, ps + kdo);
+        copy16(dstp + wave * 2 * PAIRB + PAIRB, ps + 2 * KROWB + kdo);
+      }
     } else {
       const int tl = k_end - 1;
 #pragma unroll
@@ -167,7 +179,9 @@ __global__ __launch_bounds__(64 * kWavesWide, 1) void attn_bf16_d256_vt_kernel(
         const int t = min(kt + key, tl);
         const uint64_t pp = (uint32_t)pg[(t >> kPageShift) - pg0];
         const uint32_t c = (uint32_t)(slot ^ h1);
-        dma_v(dst + i * PAIRB, kbytes + pp * pbytes + (uint32_t)(t & (kPage - 1)) * KROWB + c * 16);
+        const char *from = kbytes + pp * pbytes + (uint32_t)(t & (kPage - 1)) * KROWB + c * 16;
+        if constexpr (DMA) dma_v(dst + i * PAIRB, from);
+        else copy16(dstp + wave * 2 * PAIRB + i * PAIRB, from);
       }
     }
   };
@@ -177,8 +191,13 @@ __global__ __launch_bounds__(64 * kWavesWide, 1) void attn_bf16_d256_vt_kernel(
     // page is read and those keys are zeroed after arrival
     const uint32_t col = ((uint32_t)vpage * kPage + 8u * (vchunk & 1)) * 2u;
     const uint32_t vo = vrow0 + col;
-    dma_s<0>(dst, vtbytes, vo);
-    dma_s<0>(dst + 1024, vtbytes, vo + vrow_step);
+    if constexpr (DMA) {
+      dma_s<0>(dst, vtbytes, vo);
+      dma_s<0>(dst + 1024, vtbytes, vo + vrow_step);
+    } else {
+      copy16(dstp + wave * 32 * VROWB, vtbytes + vo);
+      copy16(dstp + wave * 32 * VROWB + 1024, vtbytes + (uint32_t)(vo + vrow_step));
+    }
   };
   // zero the V^T entries of keys past k_end in a landed partial tile: lanes 0..31 of wave w take
   // the feature rows 32w .. 32w + 31 that this wave loaded
@@ -438,11 +457,13 @@ hipError_t launch_attn_d256_vt(const AttnArgs &args, const AttnPlan &plan, int n
                                hipStream_t stream) {
   const dim3 grid(plan.units_per_head * n_kv);
   const dim3 block(64 * kWavesWide);
-  if (cap)
-    hipLaunchKernelGGL(attn_bf16_d256_vt_kernel<true>, grid, block, 0, stream, args, plan);
-  else
-    hipLaunchKernelGGL(attn_bf16_d256_vt_kernel<false>, grid, block, 0, stream, args, plan);
-  return hipGetLastError();
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, args, plan);
+    return hipGetLastError();
+  };
+  if ((uintptr_t)args.kc % 16 != 0 || (uintptr_t)args.vc % 16 != 0)
+    return cap ? run(attn_bf16_d256_vt_kernel<true, false>) : run(attn_bf16_d256_vt_kernel<false, false>);
+  return cap ? run(attn_bf16_d256_vt_kernel<true, true>) : run(attn_bf16_d256_vt_kernel<false, true>);
 }
 
 }  // namespace nexus

@@ -59,7 +59,7 @@ def test_pieces(d, vt, cap, n_s, n_past):
     assert ma <= BF16_MAX_ABS and rr <= BF16_REL_RMS, (ma, rr)
 
 
-@pytest.mark.parametrize("d,vt", [(64, False), (64, True), (128, False), (128, True)])
+@pytest.mark.parametrize("d,vt", [(64, False), (64, True), (128, False), (128, True), (256, False), (256, True)])
 def test_cache_base_not_16_byte_aligned(d, vt):
     """The same bits from a cache that starts 2 bytes past a 16-byte boundary."""
     n_kv, g, n_s, n_past = 2, 2, 75, 700

@@ -225,3 +225,19 @@ def _own_bytes(n, kv, g, d, tokens):
         splits = 256 // pairs
         splits = -(-pages // -(-pages // splits))
     return n * kv * g * splits * (d + 2) * 4 if splits > 1 else 1
+
+
+@pytest.mark.parametrize("d,kv,layout,n,tokens", [(128, 8, "rowmajor", 9, 15000), (64, 2, "transposed", 3, 900),
+                                                  (256, 8, "transposed", 1, 2000)])
+def test_cache_base_not_16_byte_aligned(d, kv, layout, n, tokens):
+    """A cache that starts 2 bytes past a 16-byte boundary, with and without shared pages to look for."""
+    t = Batch(d, kv, 3, [tokens - 20 * b for b in range(n)], [(range(n), tokens // 20)], layout)
+    for name in ("k", "v"):
+        x = getattr(t, name)
+        pool = torch.zeros(x.numel() + 8, dtype=x.dtype, device="cuda")
+        y = pool[1:1 + x.numel()].view(x.shape)
+        y.copy_(x)
+        assert y.data_ptr() % 16 == 2
+        setattr(t, name, y)
+    sel = sorted({0, n // 2, n - 1})
+    _check(t.run()[sel], t.oracle(sel), "bf16", f"head_dim {d} {layout}, base at 2 bytes")

@@ -1126,6 +1126,8 @@ DecodeShape decode_shape(const DecodeLaunch &p, size_t ws_bytes) {
   // looked for 114).  A look costs 1 to 2 us where nothing is shared.
   const int64_t kv_bytes = (int64_t)p.n_seqs * p.max_len * p.n_kv_heads * p.head_dim * 4;
   if (!p.is_bf16 || p.n_seqs < 2 || kv_bytes < (s.own_splits > 1 ? 1 : 4) * kSharedMinBytes) return s;
+  // such a launch has its workgroups in one grid dimension, which holds less than 2^32 threads
+  if ((int64_t)p.n_kv_heads * per_kv * p.n_seqs * s.own_splits > UINT32_MAX / 256) return s;
   // sequences per group: what the column blocks of a workgroup hold
   const int per_block = group >= 16 ? 1 : 16 / group;
   const int cap = std::min(kMaxGroupSeqs, kDecWaves * shared_blocks(p.head_dim) * per_block);

@@ -376,3 +376,13 @@ def test_binding_rejects_host_tensors():
     with pytest.raises(N.NexusError) as e:
         N.slb_quantize(torch.zeros(2, 64))
     assert e.value.status == N.EINVAL
+
+
+def test_decode_workspace_of_more_workgroups_than_one_grid_dimension():
+    """Looking for shared pages puts all workgroups into one grid dimension (less than 2^32 threads of
+    them in groups of 256); a launch of more keeps three dimensions and needs its splits' partials alone."""
+    L = N.lib()
+    cc = N.CKvCache(1, 1, 1, 4096, 16, 256, 64, N.BF16, 0, 0, 1e4)
+    own = lambda n, splits: n * 256 * splits * 66 * 4
+    assert L.nexus_decode_attn_workspace(65535, 256, C.byref(cc), 65536) == own(65535, 2)
+    assert L.nexus_decode_attn_workspace(32767, 256, C.byref(cc), 65536) > own(32767, 2)

@@ -26,6 +26,9 @@
 #include "attn_common.h"
 #include "launch.h"
 
+#include <stdint.h>
+
+#include <algorithm>
 #include <type_traits>
 
 namespace nexus {
@@ -41,6 +44,7 @@ struct F32Args {
   const float *kc, *vc;               // layer bases
   const int32_t *map;
   int32_t n_kv_heads, n_q_heads, group, n_seqs;
+  int32_t first_tile;                 // of this launch
   int64_t n_cols;                     // transposed V row length
   float scale, softcap;
 };
@@ -59,7 +63,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const F32Args a, cons
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, grp = lane >> 4;
   const int kvh = blockIdx.x % a.n_kv_heads;
-  const int t = blockIdx.x / a.n_kv_heads;
+  const int t = a.first_tile + blockIdx.x / a.n_kv_heads;
   int b = 0;
   while (b + 1 < a.n_seqs && t >= tab.tile_begin[b + 1]) ++b;
   const AttnSeq sq = tab.seq[b];
@@ -276,17 +280,25 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const F32Args a, cons
 namespace {
 
 template <int D, int NW>
-void launch_f32(const F32Args &a, const F32SeqTable &tab, uint32_t blocks, bool vt,
-                hipStream_t stream) {
+hipError_t launch_f32(F32Args a, const F32SeqTable &tab, int32_t tiles, bool vt, hipStream_t stream) {
   const bool cap = a.softcap > 0.f;
+  // a grid dimension holds less than 2^32 threads: more tiles than that go in several launches
+  const int32_t most = std::max(1, (int32_t)(UINT32_MAX / (64 * NW) / (uint32_t)a.n_kv_heads));
+  for (; a.first_tile < tiles; a.first_tile += most) {
+    const dim3 grid((uint32_t)std::min(tiles - a.first_tile, most) * a.n_kv_heads);
 #define NEXUS_F32(VT_, CAP_) \
-  hipLaunchKernelGGL((attn_f32_kernel<D, NW, VT_, CAP_>), dim3(blocks), dim3(64 * NW), 0, stream, a, tab)
-  if (vt) {
-    if (cap) NEXUS_F32(true, true); else NEXUS_F32(true, false);
-  } else {
-    if (cap) NEXUS_F32(false, true); else NEXUS_F32(false, false);
-  }
+  hipLaunchKernelGGL((attn_f32_kernel<D, NW, VT_, CAP_>), grid, dim3(64 * NW), 0, stream, a, tab)
+    if (vt) {
+      if (cap) NEXUS_F32(true, true); else NEXUS_F32(true, false);
+    } else {
+      if (cap) NEXUS_F32(false, true); else NEXUS_F32(false, false);
+    }
 #undef NEXUS_F32
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (most > tiles - a.first_tile) break;   // (first_tile + most might not fit)
+  }
+  return hipSuccess;
 }
 
 }  // namespace
@@ -314,19 +326,17 @@ hipError_t launch_attention_f32(const AttnLaunch &p, hipStream_t stream) {
     tiles += (p.seqs[b].len * a.group + 15) / 16;
   }
   tab.tile_begin[p.n_seqs] = tiles;
-  const uint32_t blocks = (uint32_t)tiles * p.n_kv_heads;
   // 8 waves fit two to a SIMD up to head_dim 128 (Q, O, K and V of a page take 128 registers);
   // head_dim 256 needs twice that, so 4 waves, one to a SIMD
   switch (p.head_dim) {
-    case 8: launch_f32<8, 8>(a, tab, blocks, p.v_transposed, stream); break;
-    case 16: launch_f32<16, 8>(a, tab, blocks, p.v_transposed, stream); break;
-    case 32: launch_f32<32, 8>(a, tab, blocks, p.v_transposed, stream); break;
-    case 64: launch_f32<64, 8>(a, tab, blocks, p.v_transposed, stream); break;
-    case 128: launch_f32<128, 8>(a, tab, blocks, p.v_transposed, stream); break;
-    case 256: launch_f32<256, 4>(a, tab, blocks, p.v_transposed, stream); break;
+    case 8: return launch_f32<8, 8>(a, tab, tiles, p.v_transposed, stream);
+    case 16: return launch_f32<16, 8>(a, tab, tiles, p.v_transposed, stream);
+    case 32: return launch_f32<32, 8>(a, tab, tiles, p.v_transposed, stream);
+    case 64: return launch_f32<64, 8>(a, tab, tiles, p.v_transposed, stream);
+    case 128: return launch_f32<128, 8>(a, tab, tiles, p.v_transposed, stream);
+    case 256: return launch_f32<256, 4>(a, tab, tiles, p.v_transposed, stream);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace nexus

@@ -846,10 +846,11 @@ __device__ __forceinline__ int quant_code(float x, float s) {
   const float c = s > 0.f ? rintf(x / s) : 0.f;
   return (int)fminf(fmaxf(c, -127.f), 127.f);
 }
-// QUADS: rows of up to 1024 features in whole, aligned float4s: the row is read once, all its loads
-// in flight together, and stays in registers; else two passes, a feature per lane at a time.  The
-// loads' latency bounds a small batch: 256 rows of 768: 8.4 -> 4.2 us; a registry of
-// 65536 rows: 126 -> 52 us.
+// QUADS: rows of 65 to 1024 features in whole, aligned float4s: the row is read once, all its loads
+// in flight together, and stays in registers; else two passes, a feature per lane at a time, which is
+// the faster way where a lane has one feature anyway (100000 rows of 64: 18.6 us, as quads 23.7; of 128
+// 27.0 and 24.4).  The loads' latency bounds a small batch: 256 rows of 768: 8.4 -> 4.2 us; a
+// registry of 65536 rows: 126 -> 52 us.
 template <bool QUADS>
 __global__ __launch_bounds__(256) void slb_quantize_kernel(const float *x, int32_t n, int32_t dim,
                                                            int8_t *q, float *scale) {
@@ -988,7 +989,7 @@ size_t slb_workspace_bytes(int32_t n_tools, int32_t n_queries, int32_t dim, int3
 
 hipError_t launch_slb_quantize(const float *x, int32_t n, int32_t dim, int8_t *q, float *scale,
                                hipStream_t stream) {
-  const bool quads = dim % 4 == 0 && dim <= 1024 && (uintptr_t)x % 16 == 0 && (uintptr_t)q % 4 == 0;
+  const bool quads = dim % 4 == 0 && dim > 64 && dim <= 1024 && (uintptr_t)x % 16 == 0 && (uintptr_t)q % 4 == 0;
   if (quads)
     hipLaunchKernelGGL(slb_quantize_kernel<true>, dim3((n + 3) / 4), dim3(256), 0, stream, x, n, dim,
                        q, scale);

@@ -193,8 +193,8 @@ __global__ __launch_bounds__(256) void slb_scan_kernel(SlbArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qn = lane & 15, grp = lane >> 4;
-  const int range = a.n_ranges > 1 ? blockIdx.x : 0;
-  const int q0 = a.n_ranges > 1 ? 0 : 16 * blockIdx.x, n_q = min(16, a.n_queries - q0);
+  const int range = blockIdx.y;
+  const int q0 = 16 * blockIdx.x, n_q = min(16, a.n_queries - q0);
   const int t_begin = range * a.range_tools;
   const int t_end = min(t_begin + a.range_tools, a.n_tools);
   const int dim = a.dim, steps = dim / 64, ld = dim + kQPad;
@@ -1074,7 +1074,7 @@ hipError_t launch_slb_scan(const SlbLaunch &p, hipStream_t stream) {
                      : run(slb_block_kernel<8>, slb_merge_kernel<8>);
   }
   // one 16-query block, or several over a registry of one range
-  const dim3 grid(a.n_ranges > 1 ? a.n_ranges : (p.n_queries + 15) / 16);
+  const dim3 grid((p.n_queries + 15) / 16, a.n_ranges);
   const size_t stage = (size_t)16 * (p.dim + kQPad);
   const size_t merge = (size_t)kWaves * 16 * kTop * 8;
   const size_t lds = stage > merge ? stage : merge;

@@ -36,6 +36,11 @@ bool head_dim_ok(int32_t head_dim, int esize) {
   return head_dim <= 1024;
 }
 
+// rows of a transposed V that the splices write: at most 512 bytes (head_dim 256 in bf16, 128 in f32)
+bool transposed_row_ok(const nexus_kv_cache *c) {
+  return c->v_layout != NEXUS_V_TRANSPOSED || c->head_dim * dtype_bytes(c->dtype) <= 512;
+}
+
 nexus_status check_block(const nexus_block *b) {
   if (!b || !b->k || !b->v) return NEXUS_EINVAL;
   if (b->n_layers <= 0 || b->n_tokens <= 0 || b->n_kv_heads <= 0 || b->head_dim <= 0)
@@ -260,9 +265,7 @@ nexus_status check_splice(const nexus_kv_cache *cache, const nexus_page_table *p
     return NEXUS_EROPE;
   if (offset < 0 || offset + block->n_tokens > (int64_t)pt->n_logical_pages * kPageSize)
     return NEXUS_ERANGE;
-  const int es = dtype_bytes(cache->dtype);
-  if (cache->v_layout == NEXUS_V_TRANSPOSED && (size_t)64 * (cache->head_dim + 16 / es) * es > 65536)
-    return NEXUS_ESHAPE;
+  if (!transposed_row_ok(cache)) return NEXUS_ESHAPE;
   return NEXUS_OK;
 }
 
@@ -339,9 +342,7 @@ nexus_status nexus_rope_append(const nexus_kv_cache *cache, const nexus_page_tab
   if ((int64_t)n_tokens * cache->n_kv_heads * cache->head_dim >= kMaxElems32 ||
       (int64_t)cache->n_layers * n_tokens * cache->n_kv_heads >= kMaxElems32)
     return NEXUS_ESHAPE;
-  const int es = dtype_bytes(cache->dtype);
-  if (cache->v_layout == NEXUS_V_TRANSPOSED && (size_t)64 * (cache->head_dim + 16 / es) * es > 65536)
-    return NEXUS_ESHAPE;
+  if (!transposed_row_ok(cache)) return NEXUS_ESHAPE;
   RopeSpliceLaunch L = rope_splice_launch(cache, pt, k, v, n_tokens, offset);
   L.per_token = true;
   L.angle0 = pos0;

@@ -65,8 +65,11 @@ __global__ __launch_bounds__(256) void splice_rows_kernel(
 // inside [offset, offset + n_tokens) are written.
 // The pieces bound it: where logical pages are neighbours in memory, pieces of several pages make up
 // a cache line, so all pages of a (layer, head) go to one XCD (ids 8 apart), whose L2 joins them.
-// 26 layers x 512 tokens x 8 heads of 256 bf16, shuffled pages, cold caches: 76 us (through an LDS
-// tile, a head's pages over all XCDs) -> 55 us.
+// The rows are read past the caches, which keeps the lines that wait for their other pieces in them.
+// Shuffled pages, through an LDS tile with a head's pages over all XCDs, then so: 26 layers x 512 tokens x 8
+// heads of 256 bf16 cold 76 -> 55 us (the whole splice 73 -> 61, with cached reads 69); an append
+// whose tokens were just written 65 -> 50; one block spliced into the same pages over and over, which
+// cached reads would find in the last-level cache, 51 -> 59 (46).
 template <typename T>
 __global__ __launch_bounds__(256) void splice_vt_kernel(
     const T *__restrict__ bv, T *__restrict__ cvt, const int32_t *__restrict__ map,
@@ -142,8 +145,8 @@ hipError_t launch_splice(const SpliceLaunch &p, hipStream_t stream) {
     if (e != hipSuccess) return e;
   }
   if (p.v_transposed) {
-    // transposed rows of up to 1008 bytes, the entry points' limit (head_dim 252 in f32)
-    if (64u * ((uint32_t)p.head_dim * esize + 16u) > 65536u) return hipErrorInvalidValue;
+    // the entry points take transposed rows of up to 512 bytes (head_dim 256 in bf16, 128 in f32)
+    if (p.head_dim * esize > 512) return hipErrorInvalidValue;
     const int32_t n_pages = (int32_t)(((p.offset + p.n_tokens - 1) >> kPageShift) -
                                       (p.offset >> kPageShift) + 1);
     const uint32_t n_groups = (uint32_t)p.n_layers * (uint32_t)p.n_heads;

@@ -121,9 +121,14 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 # Both return plain integers, which ctypes passes for a void pointer: an object for each of a call's ten
 # pointers and a Stream object for its stream took 6 of the 29 us that quantising one query and scanning
-# 250 tools cost the host.
+# 250 tools cost the host.  The raw stream has no public accessor; without it the Stream object serves.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t):
